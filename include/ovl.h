@@ -474,7 +474,8 @@ ovl_status ovl_tuning_set(ovl_context *ctx, const int32_t *keys, const int32_t *
  * staging field) live in the fixed scratch array, so
  *   2 * round256(S_prec * V * nrhs) + (prec != OVL_F64 ? round256(192 * V * nrhs) : 0)
  * must not exceed OVL_NOALLOC_SCRATCH_BYTES (S_prec = 192, 96, 52 bytes per
- * site for OVL_F64, OVL_F32, OVL_HALF), else OVL_ERR_ARG and no work.  The
+ * site for OVL_F64, OVL_F32, OVL_HALF; an OVL_HALF field rounded up to 16
+ * bytes), else OVL_ERR_ARG and no work.  The
  * context must hold a gauge field (ovl_gauge_load / _generate, which do
  * allocate, at set-up).  A stencil launch shape not yet timed by the context
  * is not timed here: the fixed shape is used (same values).  The array is

@@ -146,10 +146,11 @@ struct Context {
     ~Context();
 };
 
-// Bytes of one packed spinor field.
+// Bytes of one packed spinor field: the fields' stride, in FP16 storage 52 per
+// site rounded up to 16.
 inline size_t field_bytes(const Geom &g, int prec)
 {
-    return prec == OVL_F64 ? (size_t)g.V * 192 : prec == OVL_F32 ? (size_t)g.V * 96 : (size_t)g.V * 52;
+    return prec == OVL_F64 ? (size_t)g.V * 192 : prec == OVL_F32 ? (size_t)g.V * 96 : ((size_t)g.V * 52 + 15) / 16 * 16;
 }
 
 // Blocks of 256 threads covering V sites.

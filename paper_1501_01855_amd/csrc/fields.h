@@ -112,7 +112,8 @@ template <typename ST> __host__ __device__ __forceinline__ int64_t fstride(int64
 {
     return (int64_t)Planes<ST>::n * V;
 }
-template <> __host__ __device__ __forceinline__ int64_t fstride<h8>(int64_t V) { return 3 * V + V / 4; }
+// (the scales rounded up to a whole 16-byte word, so that the next field starts after them)
+template <> __host__ __device__ __forceinline__ int64_t fstride<h8>(int64_t V) { return 3 * V + (V + 3) / 4; }
 
 __device__ __forceinline__ float2 h2f2(uint32_t w)
 {
