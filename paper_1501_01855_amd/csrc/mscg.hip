@@ -2,16 +2,23 @@
 // lowest kernel eigenvectors treated exactly (Sec. 1 after eq. 4), the
 // shifted inversions of K^2 + sigma_l done by one multi-shift CG.
 //
-// One CG iteration is four launches on the context's stream; the recurrence
+// One CG iteration is three launches on the context's stream; the recurrence
 // scalars live in device memory (mscg_state.h) so the host never waits inside
 // the loop:
 //   1. t = K p                                  (stencil)
-//   2. w = K t + s0 p, (p, w) per tile          (stencil + fused dot)
-//   3. alpha = rr/(p, w); r' = r - alpha w;     (every block reduces the
-//      ||r'||^2 per block                        tile partials itself)
-//   4. beta, zeta_l', alpha_l, beta_l;          (one pass over the active
-//      y += sum_l omega_l alpha_l p_l,              shift vectors; block 0
-//      p_l = zeta_l' r' + beta_l p_l                writes the next state)
+//   2. w = K t + s0 p, (p, w) per tile          (stencil + fused dots)
+//   3. alpha = rr/(p, w), beta; r' = r - alpha w;  (every block reduces the
+//      p = r' + beta p of the smallest shift        tile partials itself;
+//      zeta_l', alpha_l, beta_l of every shift      block 0 writes the state)
+// and, once per group of up to eight iterations, one pass over the shift
+// vectors that applies the group's updates to each of them in turn:
+//   4. y += sum_l omega_l alpha_l p_l,  p_l = zeta_l' r' + beta_l p_l
+// Only the smallest shift's p enters the next iteration's K, so the others can
+// wait: the group's residuals r' are kept (a ring of fields instead of one) and
+// a shift vector is read and written once per group instead of once per
+// iteration.  The sums over shifts and iterations are the same; only y's terms
+// are added in another order, and with FP16 storage a shift vector is rounded
+// once per group.
 // Only y = sum_l omega_l x_l is stored, never the x_l themselves.  A shift is
 // frozen once omega_l |zeta_l| ||r|| / (2 sqrt(sigma_l)) <= eta ||b|| / N_Z,
 // which bounds the error of the rational function by eta ||b||.  The host
@@ -22,6 +29,7 @@
 #include <cstring>
 #include <initializer_list>
 #include <string>
+#include <type_traits>
 
 #include "context.h"
 #include "fields.h"
@@ -57,8 +65,14 @@ __global__ void k_mscg_init(MscgScal *S, int *stop, const double *partial, int n
     __shared__ double lds[4];
     const int f = blockIdx.x;
     const double b2 = block_allsum(partial + (int64_t)f * nblk, nblk, lds);
-    if (threadIdx.x != 0) return;
     MscgScal &s = S[f];   // parity 0
+    if ((int)threadIdx.x < k.nz) {
+        const int l = threadIdx.x;
+        s.zeta[l] = 1.0;
+        s.zeta_old[l] = 1.0;
+        s.act[l] = b2 > 0.0 ? 1 : 0;
+    }
+    if (threadIdx.x != 0) return;
     s.rr = b2;
     // the freezing test uses eta_f^2 ||b||^2; eta_f <= 0 marks a field to skip
     const double e2 = eta2.e2[f];
@@ -68,11 +82,6 @@ __global__ void k_mscg_init(MscgScal *S, int *stop, const double *partial, int n
     s.iters = 0;
     s.breakdown = 0;
     s.act_total = 0;
-    for (int l = 0; l < k.nz; ++l) {
-        s.zeta[l] = 1.0;
-        s.zeta_old[l] = 1.0;
-        s.act[l] = b2 > 0.0 ? 1 : 0;
-    }
     const int st0 = (b2 > 0.0 && e2 > 0.0) ? 0x7fffffff : 0;
     stop[f] = st0;
     if (st0 == 0) {   // nothing to iterate: report the field stopped (the host preset "running")
@@ -101,203 +110,545 @@ __global__ __launch_bounds__(256) void k_norm2(const ST *__restrict__ x, int64_t
     if (threadIdx.x == 0) partial[(int64_t)f * gridDim.x + blockIdx.x] = t;
 }
 
+// Iterations whose shift-vector updates are applied together (their residuals
+// cost 32 registers per lane, 40 in FP16 storage).
+constexpr int GROUP = 8;
+
+// One element of FP64 / FP32 storage (16 bytes: two or four reals); the
+// coefficients of the multi-shift CG are real, so its vector updates act on
+// elements whatever complex component they hold.
+__device__ __forceinline__ double2 el_axpy(double a, double2 x, double2 y) { return {y.x + a * x.x, y.y + a * x.y}; }
+__device__ __forceinline__ float4 el_axpy(float a, float4 x, float4 y)
+{
+    return {y.x + a * x.x, y.y + a * x.y, y.z + a * x.z, y.w + a * x.w};
+}
+__device__ __forceinline__ double2 el_comb(double a, double2 x, double b, double2 y)
+{
+    return {a * x.x + b * y.x, a * x.y + b * y.y};
+}
+__device__ __forceinline__ float4 el_comb(float a, float4 x, float b, float4 y)
+{
+    return {a * x.x + b * y.x, a * x.y + b * y.y, a * x.z + b * y.z, a * x.w + b * y.w};
+}
+__device__ __forceinline__ double el_norm2(double2 x) { return x.x * x.x + x.y * x.y; }
+__device__ __forceinline__ double el_norm2(float4 x)
+{
+    return (double)x.x * (double)x.x + (double)x.y * (double)x.y + (double)x.z * (double)x.z +
+           (double)x.w * (double)x.w;
+}
+
+// FP16 storage: a lane holds one 16-byte plane (four of the site's twelve
+// components) of a site, three waves apart; the site's scale joins the planes
+// through LDS.  Three times the lanes of a whole site per lane, a third of its
+// registers, and the loads stay consecutive over the wave.
+struct HPlane {
+    uint4 q;
+    float sc;
+};
+__device__ __forceinline__ HPlane ld_plane(const h8 *p, int64_t V, int k, int64_t s)
+{
+    return {p[k * V + s].v, reinterpret_cast<const float *>(p + 3 * V)[s]};
+}
+__device__ __forceinline__ void plane_values(const HPlane &h, float v[8])
+{
+    const uint32_t w[4] = {h.q.x, h.q.y, h.q.z, h.q.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const float2 a = h2f2(w[c]);
+        v[2 * c] = a.x * h.sc;
+        v[2 * c + 1] = a.y * h.sc;
+    }
+}
+// The site's largest component from the three planes' values (every thread of
+// the block calls it; two buffers in turn, so one barrier per call).
+template <int NS>
+__device__ __forceinline__ float site_max(const float v[8], float (*mx)[3][NS], int &turn, int k, int j)
+{
+    float m = 0.f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) m = fmaxf(m, fabsf(v[c]));
+    float (*b)[NS] = mx[turn];
+    turn ^= 1;
+    b[k][j] = m;
+    __syncthreads();
+    return fmaxf(b[0][j], fmaxf(b[1][j], b[2][j]));
+}
+// Store the plane with the site's scale m; v takes the values as stored.
+__device__ __forceinline__ void st_plane(h8 *p, int64_t V, int k, int64_t s, float v[8], float m)
+{
+    const float inv = h8_inv_scale(m);
+    uint32_t w[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        w[c] = f22h2(v[2 * c] * inv, v[2 * c + 1] * inv);
+        const float2 a = h2f2(w[c]);
+        v[2 * c] = a.x * m;
+        v[2 * c + 1] = a.y * m;
+    }
+    p[k * V + s].v = make_uint4(w[0], w[1], w[2], w[3]);
+    if (k == 0) reinterpret_cast<float *>(p + 3 * V)[s] = m;
+}
+
 // One multi-shift CG step after the two stencils of the iteration:
 //   alpha = (r, r) / (p, w)      (p, w) from the stencil's tile partials;
 //                                (r, r) exact, from the previous step's blocks
-//   r' = r - alpha w             in place; exact ||r'||^2 per block for the next step
+//   r' = r - alpha w             into the next slot of the ring of residuals;
+//                                exact ||r'||^2 per block for the next step
 //   beta = ||r'||^2 / (r, r)     with ||r'||^2 = (r, r) - 2 alpha Re (r, w)
 //                                + alpha^2 (w, w) (the stencil's other partials),
 //                                so that no step waits on a grid-wide sum of r'
-//   y += sum_l omega_l alpha_l p_l ; p_l = zeta_l' r' + beta_l p_l (active shifts)
-// On the first step every p_l is the source and y starts at zero.  With ALL,
-// y holds one solution per shift, shift-major like p, and x_l += omega_l
-// alpha_l p_l (the caller passes omega_l = 1).  Every block derives the
-// step's scalars from the same partial sums in the same order; block 0
-// stores the next state.
-template <typename ST, bool ALL>
-__global__ __launch_bounds__(256) void k_mscg_shift(const ST *__restrict__ src, const ST *__restrict__ rin,
-                                                    ST *__restrict__ r, const ST *__restrict__ w,
-                                                    ST *__restrict__ y, ST *__restrict__ p, MscgScal *S,
-                                                    const MscgConst *kc, int *stop, MscgFinal *fin,
-                                                    const int *itb, int itj, int64_t V, const double *part,
-                                                    int pw_n, double *rr_part, int rr_n, int *stop_h,
-                                                    MscgFinal *fin_h)
+//   p = r' + beta p              of the smallest shift, whose zeta stays 1
+// Every block derives the scalars from the same partial sums in the same
+// order; block 0 also advances the recurrences of the other shifts and writes
+// the next state and the iteration's coefficients for k_mscg_flush.
+struct MscgStep {
+    MscgScal *S;
+    MscgCoef *coef;
+    int group;
+    const MscgConst *kc;
+    int *stop;
+    const int *itb;   // device iteration base (graph replays), or null
+    int itj;
+    const double *part;
+    int pw_n;
+    double *rr_part;
+    int rr_n;
+    int *stop_h;
+    MscgFinal *fin_h;
+};
+
+// The scalars of iteration it for field f; false when the field breaks down or
+// has stopped (stop: its stopping iteration, tested only once the loads are on
+// their way, as it is itself a load from memory).
+template <int NT>
+__device__ __forceinline__ bool step_scalars(const MscgStep &a, int f, int nf, int it, int stop, double &alpha,
+                                             double &beta)
 {
-    using R = typename Planes<ST>::R;
-    const int f = blockIdx.y;
-    const int it = itb ? *itb + itj : itj;   // the iteration (device base for graph replays)
-    if (it >= stop[f]) return;
-    const int nf = gridDim.y;
     // exact ||r||^2 partials by iteration parity: read this step's, write the next's
-    const double *rr_in = rr_part + (size_t)(it & 1) * rr_n * nf;
-    double *rr_out = rr_part + (size_t)((it + 1) & 1) * rr_n * nf;
-    __shared__ double lds[4];
-    __shared__ double s_cy[NZMAX], s_zn[NZMAX], s_bl[NZMAX];
-    __shared__ int s_act[NZMAX];
-    __shared__ int s_keep_any;
-    const MscgScal &sc = S[(it & 1) * nf + f];
-    const int64_t fo = f * fstride<ST>(V);
-    const int64_t s0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    // The first site's r and w do not depend on the step's scalars: their
-    // loads go out before the sums of partials, and arrive during them.
-    SpStored<ST> r_first, w_first;
-    if (s0 < V) {
-        ld_sp_stored((it == 0 ? src : rin) + fo, V, s0, r_first);
-        ld_sp_stored(w + fo, V, s0, w_first);
+    const double *rf = a.rr_part + (size_t)(it & 1) * a.rr_n * nf + (int64_t)f * a.rr_n;
+    const double *pf = a.part + (int64_t)f * 3 * a.pw_n;
+    const MscgScal &sc = a.S[(it & 1) * nf + f];
+    const int pw_n = a.pw_n, rr_n = a.rr_n, group = a.group;
+    // block 0 also advances the shifts' recurrences: their state arrives during
+    // the sums (one lane per shift; every entry exists, whatever nz)
+    const MscgConst *kc = a.kc;
+    const int l = threadIdx.x % NZMAX;
+    double z = 1.0, zo = 1.0, sig = 0.0, om = 0.0, tol2 = 0.0, al_old = 1.0, be_old = 0.0, b2 = 0.0, s0 = 0.0;
+    int was = 0, nz = 0, maxiter = 0, iters = 0, broken = 0, act_total = 0;
+    if (blockIdx.x == 0) {
+        z = sc.zeta[l];
+        zo = sc.zeta_old[l];
+        was = sc.act[l];
+        sig = kc->sigma[l];
+        om = kc->omega[l];
+        tol2 = kc->tol2[l];
+        al_old = sc.alpha_old;
+        be_old = sc.beta_old;
+        b2 = sc.b2;
+        s0 = kc->s0;
+        nz = kc->nz;
+        maxiter = kc->maxiter;
+        iters = sc.iters;
+        broken = sc.breakdown;
+        act_total = sc.act_total;
     }
+    const double rr0 = sc.rr;
     // The four sums of partials.  Each thread adds its terms in index order;
     // the loads of PB consecutive terms of each sum are issued together (an
     // index past the end reads the last entry, and adds nothing).
-    const double *pf = part + (int64_t)f * 3 * pw_n;
-    const double *rf = rr_in + (int64_t)f * rr_n;
     double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
     const int nmax = pw_n > rr_n ? pw_n : rr_n;
-    constexpr int PB = 8;
-    for (int i0 = threadIdx.x; i0 < nmax; i0 += PB * blockDim.x) {
+    constexpr int PB = 4;
+    for (int j0 = threadIdx.x; j0 < nmax; j0 += PB * NT) {
         double a0[PB], a1[PB], a2[PB], a3[PB];
 #pragma unroll
         for (int q = 0; q < PB; ++q) {
-            const int i = i0 + q * (int)blockDim.x;
-            const int ip = i < pw_n ? i : pw_n - 1, ir = i < rr_n ? i : rr_n - 1;
-            a0[q] = pf[ip];
-            a1[q] = pf[pw_n + ip];
-            a2[q] = pf[2 * pw_n + ip];
-            a3[q] = rf[ir];
+            const int j = j0 + q * NT;
+            const int jp = j < pw_n ? j : pw_n - 1, jr = j < rr_n ? j : rr_n - 1;
+            a0[q] = pf[jp];
+            a1[q] = pf[pw_n + jp];
+            a2[q] = pf[2 * pw_n + jp];
+            a3[q] = rf[jr];
         }
 #pragma unroll
         for (int q = 0; q < PB; ++q) {
-            const int i = i0 + q * (int)blockDim.x;
-            if (i < pw_n) {
+            const int j = j0 + q * NT;
+            if (j < pw_n) {
                 v0 += a0[q];
                 v1 += a1[q];
                 v2 += a2[q];
             }
-            if (it != 0 && i < rr_n) v3 += a3[q];
+            if (it != 0 && j < rr_n) v3 += a3[q];
         }
     }
+    if (it >= stop) return false;
     double vv[4] = {v0, v1, v2, v3}, tot[4];
-    block_bcast_sum4(vv, tot);
+    block_bcast_sum4<NT>(vv, tot);
     const double pw = tot[0], rw = tot[1], ww = tot[2];
-    const double rr = it == 0 ? sc.rr : tot[3];
-    const double alpha = rr / pw;
+    const double rr = it == 0 ? rr0 : tot[3];
+    alpha = rr / pw;
     const double rr_new = fmax(0.0, rr - 2.0 * alpha * rw + alpha * alpha * ww);
     const bool ok = pw > 0.0 && isfinite(alpha) && isfinite(rr_new);
-    const double beta = rr_new / rr;
-    const int nz = kc->nz;
-    if (threadIdx.x == 0) s_keep_any = 0;
-    __syncthreads();
-    if ((int)threadIdx.x < nz) {
-        const int l = threadIdx.x;
-        const int act = sc.act[l] && ok;
-        s_act[l] = act;
-        double zn = sc.zeta[l], cy = 0.0, bl = 0.0;
-        if (act) {
-            const double z = sc.zeta[l], zo = sc.zeta_old[l];
-            zn = (z * zo * sc.alpha_old) /
-                 (alpha * sc.beta_old * (zo - z) + zo * sc.alpha_old * (1.0 + (kc->sigma[l] - kc->s0) * alpha));
-            cy = kc->omega[l] * (alpha * zn / z);
-            const double q = zn / z;
-            bl = beta * q * q;
-        }
-        s_zn[l] = zn;
-        s_cy[l] = cy;
-        s_bl[l] = bl;
-        if (blockIdx.x == 0) {
-            MscgScal &nx = S[((it + 1) & 1) * nf + f];
-            nx.zeta_old[l] = act ? sc.zeta[l] : sc.zeta_old[l];
+    beta = rr_new / rr;
+    if (blockIdx.x == 0) {   // the shifts' recurrences (the whole block takes this branch)
+        __shared__ int s_act[NZMAX];
+        __shared__ int s_keep_any;
+        MscgScal &nx = a.S[((it + 1) & 1) * nf + f];
+        if (threadIdx.x == 0) s_keep_any = 0;
+        __syncthreads();
+        if ((int)threadIdx.x < nz) {   // NT >= NZMAX >= nz
+            const int act = was && ok;
+            s_act[l] = act;
+            double zn = z, cy = 0.0, bl = 0.0;
+            if (act) {
+                zn = (z * zo * al_old) / (alpha * be_old * (zo - z) + zo * al_old * (1.0 + (sig - s0) * alpha));
+                const double q = zn / z;
+                cy = om * (alpha * zn / z);
+                bl = beta * q * q;
+            }
+            MscgCoef &cf = a.coef[(int64_t)f * group + it % group];
+            cf.cy[l] = cy;
+            cf.zn[l] = zn;
+            cf.bl[l] = bl;
+            cf.act[l] = act;
+            nx.zeta_old[l] = act ? z : zo;
             nx.zeta[l] = zn;
-            const int keep = act && !(zn * zn * rr_new <= kc->tol2[l] * sc.b2);
+            const int keep = act && !(zn * zn * rr_new <= tol2 * b2);
             nx.act[l] = keep;
             if (keep) atomicOr(&s_keep_any, 1);
         }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int na = 0;
+            if (it % group == 0)
+                for (int q = 0; q < nz; ++q) na += s_act[q];
+            broken = broken || !ok;
+            iters += 1;
+            act_total += na;
+            nx.rr = rr_new;
+            nx.b2 = b2;
+            nx.alpha_old = alpha;
+            nx.beta_old = beta;
+            nx.iters = iters;
+            nx.breakdown = broken;
+            nx.act_total = act_total;
+            if (!s_keep_any || broken || iters >= maxiter) {
+                // host memory is written once per field and call, when it stops;
+                // the counts reach the host before the flag
+                a.fin_h[f] = MscgFinal{iters, broken, act_total, 0};
+                __threadfence_system();
+                a.stop[f] = it + 1;
+                a.stop_h[f] = it + 1;
+                __threadfence_system();   // complete before the kernel is
+            }
+        }
+    }
+    return ok;
+}
+
+// FP64 and FP32.  Memory-bound, five fields moved; 1024 threads per block on
+// large lattices, because every block reads all partials (three sums over up
+// to 5376 tiles on 24^3 x 48): larger blocks are fewer, and each thread's share
+// of the sums is one or two batches of loads.  256 on small ones, where the
+// reductions over a block are what takes the time.
+template <typename ST, int NT>
+__global__ __launch_bounds__(NT) void k_mscg_step(const ST *rin, ST *rout, const ST *__restrict__ w,
+                                                       const ST *pin, ST *pb, MscgStep a, int64_t V)
+{
+    using R = typename Planes<ST>::R;
+    const int f = blockIdx.y, nf = gridDim.y;
+    const int it = a.itb ? *a.itb + a.itj : a.itj;
+    const int stop = a.stop[f];   // tested once the first loads are on their way
+    const int64_t fo = f * fstride<ST>(V);
+    const int64_t n = Planes<ST>::n * V;
+    int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x;
+    // Two elements per thread and pass.  The first pass's loads do not depend
+    // on the step's scalars: they go out before the sums of partials, and
+    // arrive during them.
+    const int64_t step = (int64_t)gridDim.x * NT;
+    ST rv[2]{}, wv[2]{}, pv[2]{};
+    auto load = [&] {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (i + q * step < n) {
+                const int64_t o = fo + i + q * step;
+                rv[q] = rin[o];
+                wv[q] = w[o];
+                pv[q] = pin[o];
+            }
+    };
+    load();
+    double alpha, beta;
+    if (!step_scalars<NT>(a, f, nf, it, stop, alpha, beta)) return;
+    const R ar = (R)alpha, br = (R)beta;
+    double rn = 0.0;
+    while (i < n) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (i + q * step < n) {
+                const int64_t o = fo + i + q * step;
+                rv[q] = el_axpy(-ar, wv[q], rv[q]);
+                rout[o] = rv[q];
+                rn += el_norm2(rv[q]);
+                pb[o] = el_axpy(br, pv[q], rv[q]);
+            }
+        i += 2 * step;
+        load();
+    }
+    __shared__ double lds[NT / 64];
+    const double t = block_sum<NT>(rn, lds);
+    if (threadIdx.x == 0)
+        a.rr_part[(size_t)((it + 1) & 1) * a.rr_n * nf + (int64_t)f * gridDim.x + blockIdx.x] = t;
+}
+
+// FP16 storage, NS sites per block and pass, three lanes per site: 256 sites
+// (few blocks, so few readings of the partials) where the lattice fills the
+// chip with them, else 64.
+template <int NS>
+__global__ __launch_bounds__(3 * NS) void k_mscg_step_h(const h8 *rin, h8 *rout, const h8 *__restrict__ w,
+                                                        const h8 *pin, h8 *pb, MscgStep a, int64_t V)
+{
+    const int f = blockIdx.y, nf = gridDim.y;
+    const int it = a.itb ? *a.itb + a.itj : a.itj;
+    const int stop = a.stop[f];   // tested once the first loads are on their way
+    __shared__ float mx[2][3][NS];
+    const int64_t fo = f * fstride<h8>(V);
+    const int k = threadIdx.x / NS, j = threadIdx.x % NS;   // plane (the same for a wave) and site of the pass
+    int64_t s0 = blockIdx.x * (int64_t)NS;
+    HPlane rq{}, wq{}, pq{};
+    auto load = [&] {
+        if (s0 + j < V) {
+            rq = ld_plane(rin + fo, V, k, s0 + j);
+            wq = ld_plane(w + fo, V, k, s0 + j);
+            pq = ld_plane(pin + fo, V, k, s0 + j);
+        }
+    };
+    load();
+    double alpha, beta;
+    if (!step_scalars<3 * NS>(a, f, nf, it, stop, alpha, beta)) return;
+    const float ar = (float)alpha, br = (float)beta;
+    double rn = 0.0;
+    int turn = 0;
+    while (s0 < V) {   // the same passes for every thread of the block
+        const int64_t s = s0 + j;
+        const bool valid = s < V;
+        float rv[8], pv[8];
+        plane_values(rq, rv);
+        plane_values(wq, pv);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) rv[c] = rv[c] - ar * pv[c];
+        float m = site_max<NS>(rv, mx, turn, k, j);
+        if (valid) {
+            st_plane(rout + fo, V, k, s, rv, m);   // continue with r' as stored
+#pragma unroll
+            for (int c = 0; c < 8; ++c) rn += (double)rv[c] * (double)rv[c];
+        }
+        plane_values(pq, pv);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) pv[c] = rv[c] + br * pv[c];
+        s0 += (int64_t)gridDim.x * NS;
+        load();
+        m = site_max<NS>(pv, mx, turn, k, j);
+        if (valid) st_plane(pb + fo, V, k, s, pv, m);
+    }
+    __shared__ double lds[3 * NS / 64];
+    const double t = block_sum<3 * NS>(rn, lds);
+    if (threadIdx.x == 0)
+        a.rr_part[(size_t)((it + 1) & 1) * a.rr_n * nf + (int64_t)f * gridDim.x + blockIdx.x] = t;
+}
+
+// The shift vectors brought up to date by the group of iterations that starts
+// at it0 (a multiple of group): for the group's iterations k that the field
+// ran, in order, y += cy_l p_l and p_l = zn_l r_{k+1} + bl_l p_l over the
+// shifts active in them, each p_l held in registers through the group.  In the
+// first group every p_l starts as the source and y at zero (also for a field
+// that ran no iteration).  A p_l that no later iteration needs is not written
+// back.
+// Memory-bound: per group (cnt + 2 + 2 n_active) fields, against (2 +
+// 2 n_active) fields in every iteration when the shift vectors follow at once.
+// Measured per iteration, step and an eighth of a flush against one update of
+// everything in every iteration: 24^3 x 48, one FP64 field, sign call to 1e-10
+// with 20 poles, 105 + 74 against 485 us (the step at 6.1 TB/s); twelve FP32
+// fields of 16^3 x 32 to 1e-5, 167 + 81 against 523 us; one FP16 field of
+// 24^3 x 48 in a relaxed solve (3 to 6 poles), 29 + 10 against 43 us.
+struct MscgFlush {
+    const MscgScal *S;
+    const MscgCoef *coef;
+    int group;
+    const MscgConst *kc;
+    const int *stop;
+    const int *itb;
+    int itj;
+};
+
+// The group's work for field f: the coefficients in the arithmetic type, the
+// list of shifts active in it and in how many of its iterations each is (a
+// frozen shift stays frozen; negative where its p_l is needed no more).
+// False when the field has nothing to do.
+template <typename R>
+struct GroupWork {
+    R cy[GROUP][NZMAX], zn[GROUP][NZMAX], bl[GROUP][NZMAX];
+    int l[NZMAX], n[NZMAX], na;
+};
+template <typename R>
+__device__ __forceinline__ bool group_work(const MscgFlush &a, int f, int nf, GroupWork<R> &g, int &it0, int &cnt)
+{
+    it0 = a.itb ? *a.itb + a.itj : a.itj;
+    const int st = a.stop[f];
+    if (st <= it0 && it0 != 0) return false;
+    cnt = st - it0 < a.group ? st - it0 : a.group;
+    const int nz = a.kc->nz;
+    const MscgScal &nx = a.S[((it0 + cnt) & 1) * nf + f];
+    for (int q = threadIdx.x; q < cnt * nz; q += blockDim.x) {
+        const int k = q / nz, l = q % nz;
+        const MscgCoef &cf = a.coef[(int64_t)f * a.group + k];
+        g.cy[k][l] = (R)cf.cy[l];
+        g.zn[k][l] = (R)cf.zn[l];
+        g.bl[k][l] = (R)cf.bl[l];
+    }
+    if (threadIdx.x < 64) {   // one wave: NZMAX = 64 shifts
+        const int l = threadIdx.x;
+        int na = 0;
+        if (l < nz)
+            for (int k = 0; k < cnt; ++k) na += a.coef[(int64_t)f * a.group + k].act[l] != 0;
+        const unsigned long long m = __ballot(na > 0);
+        if (na > 0) {
+            const int at = __popcll(m & ((1ull << l) - 1));
+            g.l[at] = l;
+            g.n[at] = st > it0 + cnt && nx.act[l] ? na : -na;
+        }
+        if (l == 0) g.na = __popcll(m);
     }
     __syncthreads();
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        MscgScal &nx = S[((it + 1) & 1) * nf + f];
-        int na = 0;
-        for (int l = 0; l < nz; ++l) na += s_act[l];
-        nx.rr = rr_new;
-        nx.b2 = sc.b2;
-        nx.alpha_old = alpha;
-        nx.beta_old = beta;
-        nx.iters = sc.iters + 1;
-        nx.breakdown = sc.breakdown || !ok;
-        nx.act_total = sc.act_total + na;
-        const MscgFinal fv{nx.iters, nx.breakdown, nx.act_total, 0};
-        fin[f] = fv;
-        if (!s_keep_any || nx.breakdown || nx.iters >= kc->maxiter) {
-            // host memory is written once per field and call, when it stops;
-            // the counts reach the host before the flag
-            fin_h[f] = fv;
-            __threadfence_system();
-            stop[f] = it + 1;
-            stop_h[f] = it + 1;
-            __threadfence_system();   // complete before the kernel is
-        }
-    }
-    if (!ok) return;
-    const int64_t pstride = nf * fstride<ST>(V);   // shift-major: p[l][f]
-    const R ar = (R)alpha;
-    double rn = 0.0;
-    // one site, from its loaded r and w
-    auto site = [&](int64_t s, cplx<R> (&rv)[12], cplx<R> (&pv)[12]) {
-        cplx<R> yv[12];
+    return true;
+}
+
+// FP64 and FP32, element by element.  With ALL, y holds one solution per
+// shift, shift-major like p, and x_l += cy_l p_l (the caller passes
+// omega_l = 1).
+template <typename ST, bool ALL>
+__global__ __launch_bounds__(256) void k_mscg_flush(const ST *__restrict__ src, const ST *__restrict__ ring,
+                                                    ST *__restrict__ y, ST *__restrict__ p, MscgFlush a, int64_t V)
+{
+    using R = typename Planes<ST>::R;
+    const int f = blockIdx.y, nf = gridDim.y;
+    __shared__ GroupWork<R> g;
+    int it0, cnt;
+    if (!group_work(a, f, nf, g, it0, cnt)) return;
+    const bool first = it0 == 0;
+    const int na = g.na;
+    const int64_t fo = f * fstride<ST>(V);
+    const int64_t fstep = (int64_t)nf * fstride<ST>(V);   // shift-major p[l][f]; ring slots likewise
+    const int64_t n = Planes<ST>::n * V;
+    const ST zero = el_comb(R(0), ST{}, R(0), ST{});
+    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        ST rk[GROUP];
 #pragma unroll
-        for (int c = 0; c < 12; ++c) rv[c] = rv[c] - ar * pv[c];
-        st_sp(r + fo, V, s, rv);
-        as_stored(r, rv, 12);   // continue with r' as stored
+        for (int k = 0; k < GROUP; ++k)
+            if (k < cnt) rk[k] = ring[((k + 1) % a.group) * fstep + fo + i];
+        ST yv = zero, sv = zero;
+        if (first)
+            sv = src[fo + i];
+        else if constexpr (!ALL)
+            yv = y[fo + i];
+        constexpr int LB = 4;   // shift vectors whose loads are in flight together
+        for (int a0 = 0; a0 < na; a0 += LB) {
+            ST pv[LB], xv[LB];
 #pragma unroll
-        for (int c = 0; c < 12; ++c) rn += (double)rv[c].re * (double)rv[c].re + (double)rv[c].im * (double)rv[c].im;
-        if (it == 0) {
-#pragma unroll
-            for (int c = 0; c < 12; ++c) yv[c] = {R(0), R(0)};
-            ld_sp(src + fo, V, s, pv);
-        } else if constexpr (!ALL) {
-            ld_sp(y + fo, V, s, yv);
-        }
-        for (int l = 0; l < nz; ++l) {
-            if (!s_act[l]) continue;
-            ST *pl = p + l * pstride + fo;
-            if (it != 0) ld_sp(pl, V, s, pv);
-            const R cy = (R)s_cy[l], zn = (R)s_zn[l], bl = (R)s_bl[l];
-            if constexpr (ALL) {
-                ST *xl = y + l * pstride + fo;
-                cplx<R> xv[12];
-                if (it != 0) {
-                    ld_sp(xl, V, s, xv);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 12; ++c) xv[c] = {R(0), R(0)};
+            for (int b = 0; b < LB; ++b) {
+                pv[b] = sv;
+                xv[b] = zero;
+                if (a0 + b < na && !first) {
+                    const int64_t o = g.l[a0 + b] * fstep + fo + i;
+                    pv[b] = p[o];
+                    if constexpr (ALL) xv[b] = y[o];
                 }
-#pragma unroll
-                for (int c = 0; c < 12; ++c) xv[c] = xv[c] + cy * pv[c];
-                st_sp(xl, V, s, xv);
-            } else {
-#pragma unroll
-                for (int c = 0; c < 12; ++c) yv[c] = yv[c] + cy * pv[c];
             }
-            cplx<R> nv[12];
 #pragma unroll
-            for (int c = 0; c < 12; ++c) nv[c] = zn * rv[c] + bl * pv[c];
-            st_sp(pl, V, s, nv);
+            for (int b = 0; b < LB; ++b) {
+                if (a0 + b >= na) continue;
+                const int l = g.l[a0 + b], nl = g.n[a0 + b], kn = nl < 0 ? -nl : nl;
+                ST xl = ALL ? xv[b] : yv;
+#pragma unroll
+                for (int k = 0; k < GROUP; ++k) {
+                    if (k >= kn) continue;
+                    xl = el_axpy(g.cy[k][l], pv[b], xl);
+                    pv[b] = el_comb(g.zn[k][l], rk[k], g.bl[k][l], pv[b]);
+                }
+                const int64_t o = l * fstep + fo + i;
+                if (nl > 0) p[o] = pv[b];
+                if constexpr (ALL)
+                    y[o] = xl;
+                else
+                    yv = xl;
+            }
         }
-        if constexpr (!ALL) st_sp(y + fo, V, s, yv);
-    };
-    const int64_t step = (int64_t)gridDim.x * blockDim.x;
-    if (s0 < V) {
-        cplx<R> rv[12], pv[12];
-        sp_values(r_first, rv);
-        sp_values(w_first, pv);
-        site(s0, rv, pv);
+        if constexpr (!ALL)
+            y[fo + i] = yv;
+        else if (cnt == 0)   // a field with no iteration: its solutions are zero
+            for (int l = 0; l < a.kc->nz; ++l) y[l * fstep + fo + i] = zero;
     }
-    for (int64_t s = s0 + step; s < V; s += step) {
-        cplx<R> rv[12], pv[12];
-        ld_sp((it == 0 ? src : rin) + fo, V, s, rv);
-        ld_sp(w + fo, V, s, pv);
-        site(s, rv, pv);
+}
+
+// FP16 storage: three lanes per site as in the step; a p_l and y are rounded
+// to FP16 once per group.
+template <int NS>
+__global__ __launch_bounds__(3 * NS) void k_mscg_flush_h(const h8 *__restrict__ src, const h8 *__restrict__ ring,
+                                                         h8 *__restrict__ y, h8 *__restrict__ p, MscgFlush a,
+                                                         int64_t V)
+{
+    const int f = blockIdx.y, nf = gridDim.y;
+    __shared__ GroupWork<float> g;
+    __shared__ float mx[2][3][NS];
+    int it0, cnt;
+    if (!group_work(a, f, nf, g, it0, cnt)) return;
+    const bool first = it0 == 0;
+    const int na = g.na;
+    const int64_t fo = f * fstride<h8>(V);
+    const int64_t fstep = (int64_t)nf * fstride<h8>(V);
+    const int k3 = threadIdx.x / NS, j = threadIdx.x % NS;
+    int turn = 0;
+    for (int64_t s0 = blockIdx.x * (int64_t)NS; s0 < V; s0 += (int64_t)gridDim.x * NS) {
+        const int64_t s = s0 + j;
+        const bool valid = s < V;
+        HPlane rk[GROUP]{}, sq{}, yq{};
+        float rv[GROUP][8], yv[8];
+        if (valid) {
+#pragma unroll
+            for (int k = 0; k < GROUP; ++k)
+                if (k < cnt) rk[k] = ld_plane(ring + ((k + 1) % a.group) * fstep + fo, V, k3, s);
+            if (first)
+                sq = ld_plane(src + fo, V, k3, s);
+            else
+                yq = ld_plane(y + fo, V, k3, s);
+        }
+        plane_values(yq, yv);   // zero in the first group
+#pragma unroll
+        for (int k = 0; k < GROUP; ++k) plane_values(rk[k], rv[k]);
+        for (int b = 0; b < na; ++b) {
+            const int l = g.l[b], nl = g.n[b], kn = nl < 0 ? -nl : nl;
+            HPlane pq = sq;
+            if (valid && !first) pq = ld_plane(p + l * fstep + fo, V, k3, s);
+            float pv[8];
+            plane_values(pq, pv);
+#pragma unroll
+            for (int k = 0; k < GROUP; ++k) {
+                if (k >= kn) continue;
+                const float cy = g.cy[k][l], zn = g.zn[k][l], bl = g.bl[k][l];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    yv[c] = yv[c] + cy * pv[c];
+                    pv[c] = zn * rv[k][c] + bl * pv[c];
+                }
+            }
+            if (nl > 0) {   // the same for the whole block
+                const float m = site_max<NS>(pv, mx, turn, k3, j);
+                if (valid) st_plane(p + l * fstep + fo, V, k3, s, pv, m);
+            }
+        }
+        const float m = site_max<NS>(yv, mx, turn, k3, j);
+        if (valid) st_plane(y + fo, V, k3, s, yv, m);
     }
-    const double t = block_sum<256>(rn, lds);
-    if (threadIdx.x == 0) rr_out[(int64_t)f * gridDim.x + blockIdx.x] = t;
 }
 
 // Iteration base of graph replays: set, then advanced after each chunk.
@@ -458,19 +809,34 @@ static hipGraphExec_t chunk_graph(Context &c, int prec, int nf, bool all, int ch
 // xs[l][f] = (K^2 + sigma_l)^{-1} in_f, each to |zeta_l| ||r|| <= eta_f ||in_f||,
 // with no low-mode split and no final K.
 //
-// The update kernel's grid is the number of its blocks resident on the device
-// at once: it strides over the sites, and a larger grid would leave a partial
-// second round of blocks running after the first.
-template <typename ST, bool ALL>
-static unsigned upd_blocks(Context &c, int prec)
+// The update kernels' grids are at most the number of their blocks resident on
+// the device at once: they stride over a field, and a larger grid would leave a
+// partial second round of blocks running after the first, with one more
+// prologue each.  The step's blocks are shared among the fields of a launch
+// (its prologue reads every tile's sums: 193 -> 168 us for 12 FP32 fields of
+// 16^3 x 32); the flush, with its short prologue and one long chain of loads
+// per element, is faster with that many blocks per field (649 against 882 us).
+template <typename K>
+static unsigned resident_blocks(Context &c, int &per_cu, K *kernel, int nt)
 {
-    int &n = c.upd_per_cu[prec][ALL ? 1 : 0];
-    if (n == 0) {
+    if (per_cu == 0) {
         int b = 0;
-        OVL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_mscg_shift<ST, ALL>, 256, 0));
-        n = b > 0 ? b : 1;
+        OVL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernel, nt, 0));
+        per_cu = b > 0 ? b : 1;
     }
-    return (unsigned)(n * c.num_cu);
+    return (unsigned)(per_cu * c.num_cu);
+}
+
+// The ring of residuals: GROUP slots (iterations per group), halved while the ring would take more than a quarter of the
+// free device memory (one slot is the residual updated in place).
+static void *residual_ring(Context &c, size_t field_set, int &group)
+{
+    if (c.pool["ms_ring"].bytes < field_set * group) {
+        size_t avail = 0, total = 0;
+        OVL_HIP(hipMemGetInfo(&avail, &total));
+        while (group > 1 && field_set * group > avail / 4) group /= 2;
+    }
+    return c.buf("ms_ring", field_set * group);
 }
 
 template <typename ST>
@@ -484,8 +850,30 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
     const unsigned nblk = site_blocks(g);
     const unsigned nblk_max = (unsigned)stencil_tiles_max(g);   // tiles of any stencil variant
     const dim3 grid(nblk, nf);
-    const unsigned nupd = std::min<unsigned>(all ? upd_blocks<ST, true>(c, prec) : upd_blocks<ST, false>(c, prec), nblk);
-    const dim3 ugrid(nupd, nf);
+    // the update kernels and their grids: elements of 16 bytes, or in FP16
+    // storage three lanes per site, with 64-site blocks in the step where
+    // 256-site ones would be fewer than two per CU
+    void (*step)(const ST *, ST *, const ST *, const ST *, ST *, MscgStep, int64_t) = nullptr;
+    void (*flush)(const ST *, const ST *, ST *, ST *, MscgFlush, int64_t) = nullptr;
+    unsigned step_nt, flush_nt = 256, nstep, nflush;
+    int *const per_cu = c.upd_per_cu[prec];
+    auto share = [&](unsigned blocks) { return (blocks + nf - 1) / (unsigned)nf; };
+    if constexpr (std::is_same<ST, h8>::value) {
+        const int ns = V >= (int64_t)512 * c.num_cu ? 256 : 64;
+        step = ns == 256 ? k_mscg_step_h<256> : k_mscg_step_h<64>;
+        flush = k_mscg_flush_h<64>;
+        step_nt = 3 * ns;
+        flush_nt = 3 * 64;
+        nstep = std::min(share(resident_blocks(c, per_cu[0], step, 3 * ns)), (unsigned)((V + ns - 1) / ns));
+        nflush = std::min(resident_blocks(c, per_cu[1], flush, 3 * 64), (unsigned)((V + 63) / 64));
+    } else {
+        flush = all ? k_mscg_flush<ST, true> : k_mscg_flush<ST, false>;
+        const int64_t n = Planes<ST>::n * V;
+        step_nt = n < (int64_t)1024 * c.num_cu ? 256 : 1024;
+        step = step_nt == 256 ? k_mscg_step<ST, 256> : k_mscg_step<ST, 1024>;
+        nstep = std::min(share(resident_blocks(c, per_cu[0], step, step_nt)), (unsigned)((n + step_nt - 1) / step_nt));
+        nflush = std::min(resident_blocks(c, per_cu[all ? 2 : 1], flush, 256), (unsigned)((n + 255) / 256));
+    }
     const int nz = z.n_z;
     OVL_REQUIRE(nz >= 1 && nz <= NZMAX, OVL_ERR_ARG, "n_z out of range");
     int nact = 0;
@@ -497,21 +885,25 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
     for (int l = 0; l < nz; ++l)
         OVL_REQUIRE(z.sigma[l] > 0.0 && z.omega[l] > 0.0, OVL_ERR_ARG, "Zolotarev coefficients must be positive");
 
-    ST *src = (ST *)c.buf("ms_src", FB * nf);
-    ST *ex = (ST *)c.buf("ms_ex", FB * nf);
-    ST *r = (ST *)c.buf("ms_r", FB * nf);
+    const bool low = c.n_low > 0 && !all;
+    // the source: the input itself, or its part off the low modes (whose exact
+    // part then waits in the output until the final K)
+    const ST *src = low ? (const ST *)c.buf("ms_src", FB * nf) : (const ST *)in;
+    ST *pb = (ST *)c.buf("ms_pb", FB * nf);   // the smallest shift's p, in step with the CG
     ST *t = (ST *)c.buf("ms_t", FB * nf);
     ST *w = (ST *)c.buf("ms_w", FB * nf);
     ST *y = all ? (ST *)xs : (ST *)c.buf("ms_y", FB * nf);
     ST *p = (ST *)c.buf("ms_p", FB * nf * nz);
     const int nl = c.n_low > 0 ? c.n_low : 1;
     double *part = (double *)c.buf("ms_part", sizeof(double) * (size_t)std::max(3 * nblk_max, nblk * 2 * nl) * nf);
-    double *rr_part = (double *)c.buf("ms_part2", sizeof(double) * 2 * (size_t)nupd * nf);   // by step parity
-    double *coef = (double *)c.buf("ms_coef", sizeof(double) * (size_t)nf * 2 * nl);
+    double *rr_part = (double *)c.buf("ms_part2", sizeof(double) * 2 * (size_t)nstep * nf);   // by step parity
+    double *lcoef = (double *)c.buf("ms_coef", sizeof(double) * (size_t)nf * 2 * nl);
     MscgScal *S = (MscgScal *)c.buf("ms_scal", sizeof(MscgScal) * 2 * nf);
-    MscgFinal *fin = (MscgFinal *)c.buf("ms_fin", sizeof(MscgFinal) * nf);
     int *stop = (int *)c.buf("ms_stop", sizeof(int) * nf);
     MscgConst *kdev = (MscgConst *)c.buf("ms_const", sizeof(MscgConst));
+    MscgCoef *coef = (MscgCoef *)c.buf("ms_cring", sizeof(MscgCoef) * GROUP * nf);
+    int group = GROUP;
+    ST *ring = (ST *)residual_ring(c, FB * nf, group);
 
     // pinned staging: constants, accuracies, and two slots of polled flags
     OVL_REQUIRE(nf <= MS_MAXF, OVL_ERR_ARG, "too many fields in one multi-shift solve");
@@ -526,17 +918,15 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
 
     // 1. low-mode split: src = (1 - P) in, ex = sum sign(lambda) P in, with the
     //    basis stored like the fields (its rounding is that of the call)
-    const bool low = c.n_low > 0 && !all;
     if (low) {
         const ST *basis = (const ST *)c.low_basis(prec);
         const double *sgn = c.low_signs();
         k_low_dots<ST><<<grid, 256, 0, c.stream>>>(basis, c.n_low, (const ST *)in, V, part);
-        k_reduce_rows<<<nf * c.n_low * 2, 256, 0, c.stream>>>(part, nblk, coef);
-        k_low_project<ST><<<grid, 256, 0, c.stream>>>(basis, c.n_low, coef, sgn, (const ST *)in, src, ex, V);
-    } else {
-        OVL_HIP(hipMemcpyAsync(src, in, FB * nf, hipMemcpyDeviceToDevice, c.stream));
+        k_reduce_rows<<<nf * c.n_low * 2, 256, 0, c.stream>>>(part, nblk, lcoef);
+        k_low_project<ST><<<grid, 256, 0, c.stream>>>(basis, c.n_low, lcoef, sgn, (const ST *)in,
+                                                         const_cast<ST *>(src), (ST *)out, V);
+        OVL_HIP(hipGetLastError());
     }
-    OVL_HIP(hipGetLastError());
 
     // 2. constants (uploaded when they change) and initial state
     MscgConst k{};
@@ -559,7 +949,6 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
         OVL_HIP(hipMemcpyAsync(kdev, &k, sizeof(MscgConst), hipMemcpyHostToDevice, c.stream));
         c.ms_const_last.assign(kb, kb + sizeof(k));
     }
-    zero_fields(c, y, all ? nf * nz : nf, prec);   // stays zero for a zero source
     k_norm2<ST><<<grid, 256, 0, c.stream>>>(src, V, part);
     MscgEta ea{};
     for (int f = 0; f < nf; ++f) {
@@ -573,40 +962,46 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
     //    behind, so the queue never runs dry.  The first chunk is launched
     //    directly (it also settles the stencil launch variants); later chunks
     //    replay a graph of CHUNK iterations whose kernels read the iteration
-    //    from *itb, unless profiling (per-launch events) is on.
-    const int CHUNK = 4;
-    const size_t pst = FB * nf;   // bytes between shift vectors
-    ST *pbase = (ST *)((char *)p + pst * base);
+    //    from *itb, unless profiling (per-launch events) is on.  A replayed
+    //    chunk holds whole groups, so that its ring slots are the same.
+    const bool replay = c.use_graphs && !c.prof;
+    const int CHUNK = replay ? std::max(4, group) : 4;
+    const size_t pst = (size_t)(FB / sizeof(ST)) * nf;   // elements between ring slots
     int *itb = (int *)c.buf("ms_itb", sizeof(int));
+    auto run_flush = [&](int j0, const int *ib) {   // the group that starts at iteration *ib + j0
+        PendingEvent pe;
+        if (c.prof) c.prof_begin(pe, KERN_SHIFT, prec, 0.0);
+        launch_k(c, c.prof ? &pe : nullptr, flush, dim3(nflush, nf), dim3(flush_nt), 0, src, ring, y, p,
+                 MscgFlush{S, coef, group, kdev, stop, ib, j0}, V);
+        if (c.prof) c.prof_end(pe);
+        OVL_HIP(hipGetLastError());
+    };
     auto one_iter = [&](int j, const int *ib) {   // iteration *ib + j (ib null: iteration j)
         const bool zero = ib == nullptr && j == 0;
-        const ST *pin = zero ? src : pbase;
-        const ST *rin = zero ? src : r;
+        const ST *pin = zero ? src : pb;
+        const ST *rin = zero ? src : ring + (j % group) * pst;
         stencil(c, EPI_K, prec, pin, t, nf, rho, 0.0, nullptr, nullptr, stop, j, nullptr, ib);
         const int ntile = stencil_k2_dot(c, prec, t, w, nf, rho, k.s0, pin, rin, part, stop, j, ib);
         PendingEvent pe;
         if (c.prof) c.prof_begin(pe, KERN_SHIFT, prec, 0.0);
-        const PendingEvent *ppe = c.prof ? &pe : nullptr;
-        if (all)
-            launch_k(c, ppe, k_mscg_shift<ST, true>, ugrid, dim3(256), 0, src, rin, r, w, y, p, S, kdev, stop, fin,
-                     ib, j, V, part, ntile, rr_part, (int)nupd, hpd->stop, hpd->fin);
-        else
-            launch_k(c, ppe, k_mscg_shift<ST, false>, ugrid, dim3(256), 0, src, rin, r, w, y, p, S, kdev, stop, fin,
-                     ib, j, V, part, ntile, rr_part, (int)nupd, hpd->stop, hpd->fin);
+        launch_k(c, c.prof ? &pe : nullptr, step, dim3(nstep, nf), dim3(step_nt), 0, rin, ring + ((j + 1) % group) * pst,
+                 w, pin, pb, MscgStep{S, coef, group, kdev, stop, ib, j, part, ntile, rr_part, (int)nstep, hpd->stop, hpd->fin},
+                 V);
         if (c.prof) c.prof_end(pe);
         OVL_HIP(hipGetLastError());
+        if ((j + 1) % group == 0) run_flush(j + 1 - group, ib);
     };
     hipGraphExec_t gexec = nullptr;
     int it = 0;
     int pending = -1;
     bool done = false;
     while (!done) {
-        if (it == 0 || c.prof || !c.use_graphs) {
+        if (it == 0 || !replay) {
             for (int j = 0; j < CHUNK; ++j) one_iter(it + j, nullptr);
         } else {
             if (!gexec) gexec = chunk_graph(c, prec, nf, all, CHUNK, itb, [&](int j) { one_iter(j, itb); },
-                                            {src, r, t, w, y, p, S, kdev, stop, fin, part, rr_part, hpd,
-                                             (const void *)(intptr_t)base, (const void *)(intptr_t)nupd},
+                                            {src, ring, t, w, y, p, pb, S, kdev, coef, stop, part, rr_part, hpd,
+                                             (const void *)(intptr_t)group, (const void *)(intptr_t)nstep},
                                             {rho, k.s0});
             if (it == CHUNK) {
                 k_set_it<<<1, 64, 0, c.stream>>>(itb, it);
@@ -631,11 +1026,17 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
             done = true;
         }
     }
+    if (it % group != 0) {   // the last, partial group, unless every field stopped before it
+        int last = 0;
+        for (int f = 0; f < nf; ++f) last = std::max(last, (int)hp.stop[f]);
+        const int j0 = it - it % group;
+        if (j0 == 0 || last > j0) run_flush(j0, nullptr);
+    }
 
-    // 4. s = K y + ex
+    // 4. s = K y + ex, the exact part in the output already
     if (all) {
     } else if (low) {
-        stencil(c, EPI_KPLUS, prec, y, out, nf, rho, 0.0, ex, nullptr);
+        stencil(c, EPI_KPLUS, prec, y, out, nf, rho, 0.0, out, nullptr);
     } else {
         stencil(c, EPI_K, prec, y, out, nf, rho, 0.0, nullptr, nullptr);
     }
@@ -651,11 +1052,12 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
         hs[f].act_total = hp.fin[f].act_total;
     }
     if (c.prof) c.prof_collect();
-    int64_t iters = 0, act_total = 0, launches = 0;
+    int64_t iters = 0, act_total = 0, launches = 0, groups = 0;
     bool brk = false, capped = false;
     for (int f = 0; f < nf; ++f) {
         if (hstop_final[f] == 0) continue;   // zero source: no iteration ran
         iters += hs[f].iters;
+        groups += (hs[f].iters + group - 1) / group;
         launches = std::max<int64_t>(launches, hs[f].iters);
         act_total += hs[f].act_total;
         brk = brk || hs[f].breakdown;
@@ -670,12 +1072,13 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
     c.last_field_iters.assign(nf, 0);
     for (int f = 0; f < nf; ++f)
         if (hstop_final[f] != 0) c.last_field_iters[f] = hs[f].iters;
-    // algorithmic bytes of the shift kernel: r, w in, r out, y in, y out and 2
-    // per active shift (with every solution kept: r, w, r out, and p_l, x_l in
-    // and out per active shift)
+    // algorithmic bytes of the updates: r, w, p in and r, p out per iteration;
+    // the residuals once more, y in and out per group and 2 per shift active in
+    // it (with every solution kept: p_l, x_l in and out, and no y)
     if (c.prof) {
         c.slots[KERN_SHIFT][prec].bytes +=
-            all ? (double)FB * (3.0 * iters + 4.0 * act_total) : (double)FB * (5.0 * iters + 2.0 * act_total);
+            all ? (double)FB * (6.0 * iters + 4.0 * act_total)
+                : (double)FB * (6.0 * iters + 2.0 * groups + 2.0 * act_total);
         // the two stencils of each executed iteration (K, then K with the
         // shift, the dot and an extra read of p), the links read once per
         // launch however many fields it carries

@@ -15,8 +15,16 @@ constexpr int NZMAX = OVL_MAX_NZ;
 
 struct MscgScal {
     double rr, alpha_old, beta_old, b2;
-    int iters, breakdown, act_total, pad;
+    int iters, breakdown, act_total, pad;   // act_total: active shifts summed over the groups of iterations
     double zeta[NZMAX], zeta_old[NZMAX];
+    int act[NZMAX];
+};
+
+// One iteration's coefficients of every shift, kept until the shift vectors
+// are brought up to date: y += cy p_l, then p_l = zn r' + bl p_l, for the
+// shifts with act set.
+struct MscgCoef {
+    double cy[NZMAX], zn[NZMAX], bl[NZMAX];
     int act[NZMAX];
 };
 
@@ -39,12 +47,12 @@ __device__ inline double block_bcast_sum(double v, double *lds)
     return r;
 }
 
-// Four block sums at once (256 threads), each with the same reduction tree as
-// block_bcast_sum (so the same values), returned to every thread; one pair of
-// barriers instead of four.
+// Four block sums at once (NT threads), in a fixed order, returned to every
+// thread; one pair of barriers instead of four.
+template <int NT>
 __device__ inline void block_bcast_sum4(double v[4], double out[4])
 {
-    __shared__ double l4[4][4];   // [value][wave]
+    __shared__ double l4[4][NT / 64];   // [value][wave]
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -58,8 +66,8 @@ __device__ inline void block_bcast_sum4(double v[4], double out[4])
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         double r = 0.0;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) r += l4[k][w];
+#pragma unroll 4   // all at once would hold every wave's sums in registers
+        for (int w = 0; w < NT / 64; ++w) r += l4[k][w];
         out[k] = r;
     }
 }
