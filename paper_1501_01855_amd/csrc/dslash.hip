@@ -1437,30 +1437,65 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     if (it != c.tuned.end()) return it->second;
     if (c.no_alloc) return 1;   // timing would need workspace and events: fixed shape, not recorded
     if (c.autotune == 0) return c.tuned[key] = 1;
-    // time every variant on scratch output
+    // Time every variant on scratch output: three rounds over the variants
+    // (interleaved, so that clock drift hits them alike), five launches each; a
+    // variant counts with its best round, and is dropped once it is far behind.
+    // Launches of 15 us or more are timed back to back, as the CG issues them.
+    // Shorter ones take less time than the host takes to launch them, so that
+    // events around the five would time the host (on 8^3 x 16 in FP16 such a
+    // tuning took a 9.5 us variant for K^2 with a 5 us one on the list): they
+    // are timed one by one, by events attached to the dispatches.
     StencilArgs<ST> t = a;
     t.stop = nullptr;
     t.out = (ST *)c.buf("tune_out", field_bytes(c.g, prec) * nf);
     t.partial = (double *)c.buf("tune_part", sizeof(double) * 3 * (size_t)nf * stencil_tiles_max(c.g));
-    hipEvent_t e0 = c.event(), e1 = c.event();
-    // three rounds over the variants (interleaved, so that clock drift hits
-    // them alike), five launches each; a variant counts with its best round
-    std::vector<float> ms_best(N_VARIANTS, 1e30f);
-    for (int v = 0; v < N_VARIANTS; ++v)
-        if (stencil_variant_ok(c.g, prec, v)) launch_by_id<ST, GT, EPI>(c, v, t, U, nf);   // warm-up
-    for (int round = 0; round < 3; ++round)
-        for (int v = 0; v < N_VARIANTS; ++v) {
-            if (!stencil_variant_ok(c.g, prec, v)) continue;
-            OVL_HIP(hipEventRecord(e0, c.stream));
-            for (int r = 0; r < 5; ++r) launch_by_id<ST, GT, EPI>(c, v, t, U, nf);
-            OVL_HIP(hipEventRecord(e1, c.stream));
-            OVL_HIP(hipEventSynchronize(e1));
-            float ms = 0.f;
-            OVL_HIP(hipEventElapsedTime(&ms, e0, e1));
-            ms_best[v] = std::min(ms_best[v], ms);
+    constexpr int REPS = 5;
+    struct Events {
+        hipEvent_t e[2 * REPS] = {};
+        Events() { for (auto &x : e) OVL_HIP(hipEventCreate(&x)); }
+        ~Events() { for (auto &x : e) if (x) hipEventDestroy(x); }
+    } ev;
+    auto single = [&](int v) {   // the fastest launch's own time
+        PendingEvent pe{};
+        for (int r = 0; r < REPS; ++r) {
+            pe.a = ev.e[2 * r];
+            pe.b = ev.e[2 * r + 1];
+            launch_by_id<ST, GT, EPI>(c, v, t, U, nf, &pe);
         }
-    int best = 0;
-    for (int v = 1; v < N_VARIANTS; ++v)
+        OVL_HIP(hipEventSynchronize(pe.b));
+        float least = 1e30f;
+        for (int r = 0; r < REPS; ++r) {
+            float ms = 0.f;
+            OVL_HIP(hipEventElapsedTime(&ms, ev.e[2 * r], ev.e[2 * r + 1]));
+            least = std::min(least, ms);
+        }
+        return REPS * least;
+    };
+    auto chain = [&](int v) {   // the five launches back to back
+        OVL_HIP(hipEventRecord(ev.e[0], c.stream));
+        for (int r = 0; r < REPS; ++r) launch_by_id<ST, GT, EPI>(c, v, t, U, nf);
+        OVL_HIP(hipEventRecord(ev.e[1], c.stream));
+        OVL_HIP(hipEventSynchronize(ev.e[1]));
+        float ms = 0.f;
+        OVL_HIP(hipEventElapsedTime(&ms, ev.e[0], ev.e[1]));
+        return ms;
+    };
+    std::vector<int> ids;
+    for (int v = 0; v < N_VARIANTS; ++v)
+        if (stencil_variant_ok(c.g, prec, v)) ids.push_back(v);
+    std::vector<float> ms_best(N_VARIANTS, 1e30f);
+    for (int v : ids) launch_by_id<ST, GT, EPI>(c, v, t, U, nf);   // warm-up
+    for (int v : ids) ms_best[v] = single(v);
+    const bool small = *std::min_element(ms_best.begin(), ms_best.end()) < REPS * 0.015f;
+    if (!small)
+        for (int v : ids) ms_best[v] = chain(v);
+    for (int round = 0; round < 2; ++round) {
+        const float lead = *std::min_element(ms_best.begin(), ms_best.end());
+        for (int v : ids)
+            if (ms_best[v] < 1.3f * lead) ms_best[v] = std::min(ms_best[v], small ? single(v) : chain(v));
+    }
+    int best = ids[0];
+    for (int v : ids)
         if (ms_best[v] < ms_best[best]) best = v;
     OVL_HIP(hipGetLastError());
     return c.tuned[key] = best;
