@@ -1275,6 +1275,225 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     stencil_lds_body<ST, GT, EPI, true>(a, U, ts);
 }
 
+// ----------------------------------------------------- eight lanes per site
+// For lattices of a few thousand sites, where the other variants leave most
+// compute units idle and each lane walks eight dependent gathers one after
+// another: a block takes 64 sites with eight waves, wave d gathering hop d
+// (direction d / 2, forward for even d) of each site -- one round trip to
+// memory instead of up to eight -- and leaving the hop's upper half in LDS.
+// Waves 0..5 then add the eight hops of two of the site's twelve components
+// each, in the order of the other variants, and finish those components.
+// Latency-bound.  Measured on 8^3 x 16 (8192 sites), one lane per site, the
+// best other variant and this one: FP64 K 9.5, 4.7, 4.1 us, K^2 + sigma with
+// its dots 10.7, 5.6, 4.9 us; FP32 7.1, 4.0, 3.9 and 7.8, 4.7, 4.0 us; FP16 6.9,
+// 4.0, 4.0 and 8.0, 4.6, 4.2 us.
+constexpr int D8_SITES = 64;
+constexpr int D8_NT = 8 * D8_SITES;
+
+// Component COMP of the sum of the hops whose upper halves are g[d][6][lane].
+template <int COMP, typename R>
+__device__ __forceinline__ cplx<R> d8_sum(const cplx<R> (*g)[6][D8_SITES], int j)
+{
+    cplx<R> acc{R(0), R(0)};
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+        constexpr int C = COMP % 6;
+        const int mu = d / 2;
+        const bool fwd = d % 2 == 0;
+        if (COMP < 6) {
+            acc = acc + g[d][C][j];
+            continue;
+        }
+        // the lower half: A g forward and -A g backward (x, y, z), -g and +g (t)
+        const cplx<R> v = g[d][mu < 2 ? (C + 3) % 6 : C][j];
+        cplx<R> l;
+        if (mu == 0)
+            l = times_mi(v);
+        else if (mu == 1)
+            l = C < 3 ? -v : v;
+        else if (mu == 2)
+            l = C < 3 ? times_mi(v) : times_i(v);
+        else
+            l = -v;
+        acc = fwd ? acc + l : acc - l;
+    }
+    return acc;
+}
+
+// Components 2h, 2h + 1 of a stored spinor (h = 0..5).
+__device__ __forceinline__ void ld_pair(const double2 *p, int64_t V, int64_t s, int h, cplx<double> v[2])
+{
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const double2 t = p[(2 * h + c) * V + s];
+        v[c] = {t.x, t.y};
+    }
+}
+__device__ __forceinline__ void ld_pair(const float4 *p, int64_t V, int64_t s, int h, cplx<float> v[2])
+{
+    const float4 t = p[h * V + s];
+    v[0] = {t.x, t.y};
+    v[1] = {t.z, t.w};
+}
+__device__ __forceinline__ void ld_pair(const h8 *p, int64_t V, int64_t s, int h, cplx<float> v[2])
+{
+    const float sc = reinterpret_cast<const float *>(p + 3 * V)[s];
+    const uint2 t = reinterpret_cast<const uint2 *>(p + (h / 2) * V + s)[h % 2];
+    const float2 a = h2f2(t.x), b = h2f2(t.y);
+    v[0] = {a.x * sc, a.y * sc};
+    v[1] = {b.x * sc, b.y * sc};
+}
+// Store them; v takes the values as stored (m: the site's scale, FP16 only).
+__device__ __forceinline__ void st_pair(double2 *p, int64_t V, int64_t s, int h, cplx<double> v[2], float)
+{
+#pragma unroll
+    for (int c = 0; c < 2; ++c) p[(2 * h + c) * V + s] = make_double2(v[c].re, v[c].im);
+}
+__device__ __forceinline__ void st_pair(float4 *p, int64_t V, int64_t s, int h, cplx<float> v[2], float)
+{
+    p[h * V + s] = make_float4(v[0].re, v[0].im, v[1].re, v[1].im);
+}
+__device__ __forceinline__ void st_pair(h8 *p, int64_t V, int64_t s, int h, cplx<float> v[2], float m)
+{
+    const float inv = h8_inv_scale(m);
+    const uint32_t w0 = f22h2(v[0].re * inv, v[0].im * inv), w1 = f22h2(v[1].re * inv, v[1].im * inv);
+    reinterpret_cast<uint2 *>(p + (h / 2) * V + s)[h % 2] = make_uint2(w0, w1);
+    if (h == 0) reinterpret_cast<float *>(p + 3 * V)[s] = m;
+    const float2 a = h2f2(w0), b = h2f2(w1);
+    v[0] = {a.x * m, a.y * m};
+    v[1] = {b.x * m, b.y * m};
+}
+
+// hop d of site s: the upper half of (1 -+ gamma_mu) U psi
+template <int MU, bool FWD, typename R, typename ST, typename GT>
+__device__ __forceinline__ void d8_hop(const ST *__restrict__ in, const GT *__restrict__ U, const Geom &g, int64_t s,
+                                       cplx<R> h[6])
+{
+    const int64_t st = g.stride[MU];
+    const int32_t Lm = g.L[MU], c = (int32_t)((s / st) % Lm);
+    const int64_t nb = FWD ? (c == Lm - 1 ? s - (int64_t)(Lm - 1) * st : s + st)
+                           : (c == 0 ? s + (int64_t)(Lm - 1) * st : s - st);
+    const int64_t ls = FWD ? s : nb;   // the link's site
+    if constexpr (std::is_same<ST, h8>::value) {
+        hv2 w[12], u[9];
+        float sc;
+        ld_sp_h(in, g.V, nb, w, sc);
+        ld_link_h(U, g.Pu, MU, ls, u);
+        hop_half_h<MU, FWD>(w, sc, u, h);
+    } else {
+        cplx<R> psi[12], u[9], q[6];
+        ld_sp(in, g.V, nb, psi);
+        ld_link(U, g.Pu, MU, ls, u);
+        spin_proj<MU, FWD>(psi, q);
+        link_mul<FWD>(u, q, h);
+    }
+}
+
+template <typename ST, typename GT, int EPI>
+__global__ __launch_bounds__(D8_NT) void k_stencil_d8(StencilArgs<ST> a, const GT *__restrict__ U)
+{
+    using R = typename Planes<ST>::R;
+    __shared__ cplx<R> g[8][6][D8_SITES];
+    __shared__ float mx[6][D8_SITES];
+    __shared__ double l3[3][6];
+    unsigned tile, f;
+    tile_of_block<true>(tile, f);
+    const int it = a.itb ? *a.itb + a.it : a.it;
+    const int stop = a.stop != nullptr ? a.stop[f] : 0x7fffffff;   // tested below, with the gathers on their way
+    const int64_t V = a.g.V;
+    const int j = threadIdx.x % D8_SITES, w = threadIdx.x / D8_SITES;   // w: the wave
+    const int64_t s = (int64_t)tile * D8_SITES + j;
+    const bool valid = s < V;
+    const ST *in = a.in + f * fstride<ST>(V);
+    const bool mine = valid && w < 6;   // this lane finishes components 2w, 2w + 1 of site s
+    cplx<R> x[2], p[2], r[2], o[2];
+    if (mine) {   // own-site inputs: in flight across the barrier
+        if constexpr (EPI != EPI_HOP) ld_pair(in, V, s, w, x);
+        if constexpr (EPI == EPI_K2DOT || EPI == EPI_KPLUS) ld_pair(a.aux + f * fstride<ST>(V), V, s, w, p);
+        if constexpr (EPI == EPI_K2DOT) ld_pair(a.aux2 + f * fstride<ST>(V), V, s, w, r);
+    }
+    if (it >= stop) return;
+    if (valid) {
+        cplx<R> h[6];
+        switch (w) {
+        case 0: d8_hop<0, true>(in, U, a.g, s, h); break;
+        case 1: d8_hop<0, false>(in, U, a.g, s, h); break;
+        case 2: d8_hop<1, true>(in, U, a.g, s, h); break;
+        case 3: d8_hop<1, false>(in, U, a.g, s, h); break;
+        case 4: d8_hop<2, true>(in, U, a.g, s, h); break;
+        case 5: d8_hop<2, false>(in, U, a.g, s, h); break;
+        case 6: d8_hop<3, true>(in, U, a.g, s, h); break;
+        default: d8_hop<3, false>(in, U, a.g, s, h); break;
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) g[w][c][j] = h[c];
+    }
+    __syncthreads();
+    if (mine) {
+        switch (w) {
+        case 0: o[0] = d8_sum<0>(g, j); o[1] = d8_sum<1>(g, j); break;
+        case 1: o[0] = d8_sum<2>(g, j); o[1] = d8_sum<3>(g, j); break;
+        case 2: o[0] = d8_sum<4>(g, j); o[1] = d8_sum<5>(g, j); break;
+        case 3: o[0] = d8_sum<6>(g, j); o[1] = d8_sum<7>(g, j); break;
+        case 4: o[0] = d8_sum<8>(g, j); o[1] = d8_sum<9>(g, j); break;
+        default: o[0] = d8_sum<10>(g, j); o[1] = d8_sum<11>(g, j); break;
+        }
+        if constexpr (EPI != EPI_HOP) {
+            const R m = (R)a.diag, hh = (R)0.5, sg = EPI == EPI_K2DOT ? (R)a.sigma : R(1);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const cplx<R> d = m * x[c] - hh * o[c];
+                o[c] = w < 3 ? d : -d;   // gamma_5
+                if constexpr (EPI == EPI_K2DOT || EPI == EPI_KPLUS) o[c] = o[c] + sg * p[c];
+            }
+        }
+    }
+    float m = 0.f;
+    if constexpr (std::is_same<ST, h8>::value) {   // the site's scale, from the six lanes that hold it
+        if (mine) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) m = fmaxf(m, fmaxf(fabsf(o[c].re), fabsf(o[c].im)));
+            mx[w][j] = m;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 6; ++q) m = fmaxf(m, valid ? mx[q][j] : 0.f);
+    }
+    if (mine) st_pair(a.out + f * fstride<ST>(V), V, s, w, o, m);
+    if constexpr (EPI == EPI_K2DOT) {
+        // (p, w), Re (r, w), (w, w) on w as stored
+        double v[3] = {0.0, 0.0, 0.0};
+        if (mine) {
+            R d0 = 0, d1 = 0, d2 = 0;   // a lane's sums in the arithmetic precision, the tile's in FP64
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const R wr = o[c].re, wi = o[c].im;
+                d0 += p[c].re * wr + p[c].im * wi;
+                d1 += r[c].re * wr + r[c].im * wi;
+                d2 += wr * wr + wi * wi;
+            }
+            v[0] = (double)d0;
+            v[1] = (double)d1;
+            v[2] = (double)d2;
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
+        if (j == 0 && w < 6)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) l3[k][w] = v[k];
+        __syncthreads();
+        if (threadIdx.x < 3) {
+            const int k = threadIdx.x;
+            double t = 0.0;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) t += l3[k][q];
+            a.partial[((int64_t)f * 3 + k) * gridDim.x + tile] = t;
+        }
+    }
+}
+
 // Launch shape chosen per (precision, epilogue, nf) by timing the variants on
 // the context's lattice the first time that shape is used (autotuning).
 // Launch variants: 0 / 1 one lane per site, MAP_LEX / MAP_REMAP; 2 / 3 two
@@ -1289,7 +1508,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // backward hop of a site inside the tile reads its neighbour's link there.
 // 20 (FP16 storage) one lane per site walking a group of four fields with the
 // site's links held in registers (k_stencil_mf); 21 the same in the XCD
-// column order of 4 / 5.
+// column order of 4 / 5.  22 eight lanes per site (k_stencil_d8), on lattices
+// of at most D8_MAX_V sites: one tile is 64 sites, and every block of the
+// multi-shift CG's update reads the sums of all tiles.
+static constexpr int64_t D8_MAX_V = 65536;
 static constexpr int N_VARIANTS = OVL_STENCIL_VARIANTS;
 static bool variant_lds(int v) { return (v >= 8 && v < 12) || (v >= 16 && v < 20); }
 static int variant_tps(int v) { return (v == 2 || v == 3 || v == 5 || v == 7 || v == 13 || v == 15) ? 2 : 1; }
@@ -1327,6 +1549,7 @@ unsigned stencil_tiles(const Geom &g, int v)
 {
     const int tps = variant_tps(v);
     const int spb = 256 / tps;
+    if (v == 22) return (unsigned)((g.V + D8_SITES - 1) / D8_SITES);
     if ((v >= 12 && v < 16) || v == 20)
         return 8u * (unsigned)(((g.V + spb - 1) / spb + 7) / 8);   // 8 XCDs x their largest share
     if (variant_lds(v)) {
@@ -1347,6 +1570,7 @@ bool stencil_variant_ok(const Geom &g, int prec, int v)
     if (variant_lds(v)) return prec != OVL_F64 && g.L[3] % (1 << (v >= 16 ? v - 16 : v - 8)) == 0;
     if (v == 20) return prec == OVL_HALF;
     if (v == 21) return prec == OVL_HALF && g.col_ok;
+    if (v == 22) return g.V <= D8_MAX_V;
     return true;
 }
 
@@ -1423,6 +1647,9 @@ static void launch_by_id(Context &c, int id, const StencilArgs<ST> &a, const GT 
             } else {
                 throw Error{OVL_ERR_ARG, "stencil variants 20 and 21 are for FP16 storage"};
             }
+            break;
+        case 22:
+            launch_k(c, pe, k_stencil_d8<ST, GT, EPI>, dim3(stencil_tiles(c.g, 22), nf), dim3(D8_NT), 0, a, U);
             break;
         default: launch_tmarch<ST, GT, EPI, 2>(c, a, U, nf, pe); break;
         }

@@ -592,10 +592,11 @@ __device__ __forceinline__ void apply_A_h(hv2 v0, hv2 v1, hv2 &w0, hv2 &w1)
     }
 }
 
-// hop_term on packed halves: psi the neighbour's stored components and sc its
-// scale, u the link (W = U_mu(x) for FWD, U_mu(x - mu) otherwise)
+// The upper half g of a hop on packed halves: psi the neighbour's stored
+// components and sc its scale, u the link (W = U_mu(x) for FWD, U_mu(x - mu)
+// otherwise)
 template <int MU, bool FWD>
-__device__ __forceinline__ void hop_term_h(const hv2 psi[12], float sc, const hv2 u[9], cplx<float> acc[12])
+__device__ __forceinline__ void hop_half_h(const hv2 psi[12], float sc, const hv2 u[9], cplx<float> g[6])
 {
     // With h = psi_up -+ A psi_down (the upper half of (1 -+ gamma_mu) psi):
     // W h = sum_b W_ab h_b: re = dot2(W_ab, (h.x, -h.y)), im = dot2(W_ab, (h.y, h.x));
@@ -619,7 +620,7 @@ __device__ __forceinline__ void hop_term_h(const hv2 psi[12], float sc, const hv
                 pi[3 * k + c] = (hv2){up.y, -up.x} + (hv2){ad.y, -ad.x};
             }
         }
-    cplx<float> g[6];   // W h (FWD) or W^+ h, times the neighbour's scale
+    // g = W h (FWD) or W^+ h, times the neighbour's scale
 #pragma unroll
     for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
@@ -633,6 +634,13 @@ __device__ __forceinline__ void hop_term_h(const hv2 psi[12], float sc, const hv
             }
             g[sp * 3 + a] = {sc * re, sc * im};
         }
+}
+// hop_term on packed halves
+template <int MU, bool FWD>
+__device__ __forceinline__ void hop_term_h(const hv2 psi[12], float sc, const hv2 u[9], cplx<float> acc[12])
+{
+    cplx<float> g[6];
+    hop_half_h<MU, FWD>(psi, sc, u, g);
     spin_recon<MU, FWD>(g, acc);
 }
 
