@@ -471,8 +471,9 @@ ovl_status ovl_tuning_set(ovl_context *ctx, const int32_t *keys, const int32_t *
  * capture, serving loops, harnesses that forbid hipMalloc): the same
  * operation as ovl_wilson_dslash (out = H in, nrhs canonical fields, device
  * in/out owned by the caller), with no hipMalloc, hipFree or other allocating
- * call.  The packed copies of in and out (and, for OVL_F32 / OVL_HALF, an FP64
- * staging field) live in the fixed scratch array, so
+ * call.  The packed copy of in lives in the fixed scratch array.  The limit is
+ * that of packed copies of in and out and, for OVL_F32 / OVL_HALF, an FP64
+ * staging field:
  *   2 * round256(S_prec * V * nrhs) + (prec != OVL_F64 ? round256(192 * V * nrhs) : 0)
  * must not exceed OVL_NOALLOC_SCRATCH_BYTES (S_prec = 192, 96, 52 bytes per
  * site for OVL_F64, OVL_F32, OVL_HALF; an OVL_HALF field rounded up to 16

@@ -171,10 +171,8 @@ ovl_status ovl_wilson_dslash(ovl_context *ctx, const double *in_dev, double *out
         OVL_REQUIRE(ctx->have_gauge, OVL_ERR_STATE, "no gauge field loaded");
         const size_t FB = field_bytes(ctx->g, prec) * nrhs;
         void *a = ctx->buf("api_a", FB);
-        void *b = ctx->buf("api_b", FB);
         pack_spinor(*ctx, in_dev, a, nrhs, prec);
-        launch_hop(*ctx, a, b, nrhs, prec);
-        unpack_spinor(*ctx, b, out_dev, nrhs, prec);
+        launch_hop(*ctx, a, out_dev, nrhs, prec);
         ctx->prof_collect();
     });
 }
@@ -193,19 +191,15 @@ ovl_status ovl_wilson_dslash_noalloc(ovl_context *ctx, const double *in_dev, dou
         OVL_REQUIRE(2 * FB + TB <= (size_t)OVL_NOALLOC_SCRATCH_BYTES, OVL_ERR_ARG,
                     "fields too large for the fixed scratch: " + std::to_string(2 * FB + TB) + " bytes needed, " +
                         std::to_string((size_t)OVL_NOALLOC_SCRATCH_BYTES) + " available");
-        unsigned char *base = (unsigned char *)noalloc_scratch(ctx->device);
-        void *a = base;
-        void *b = base + FB;
-        double2 *tmp = TB ? (double2 *)(base + 2 * FB) : nullptr;
+        void *a = noalloc_scratch(ctx->device);   // the packed input; the result goes straight to out
         struct Scope {
             Context &c;
             bool prev;
             explicit Scope(Context &cc) : c(cc), prev(cc.no_alloc) { c.no_alloc = true; }
             ~Scope() { c.no_alloc = prev; }
         } scope(*ctx);
-        pack_spinor(*ctx, in_dev, a, nrhs, prec, tmp);
-        launch_hop(*ctx, a, b, nrhs, prec);
-        unpack_spinor(*ctx, b, out_dev, nrhs, prec, tmp);
+        pack_spinor(*ctx, in_dev, a, nrhs, prec);
+        launch_hop(*ctx, a, out_dev, nrhs, prec);
     });
 }
 
@@ -220,10 +214,8 @@ ovl_status ovl_kernel_K_apply(ovl_context *ctx, double rho, const double *in_dev
         OVL_REQUIRE(ctx->have_gauge, OVL_ERR_STATE, "no gauge field loaded");
         const size_t FB = field_bytes(ctx->g, prec) * nrhs;
         void *a = ctx->buf("api_a", FB);
-        void *b = ctx->buf("api_b", FB);
         pack_spinor(*ctx, in_dev, a, nrhs, prec);
-        launch_K(*ctx, rho, a, b, nrhs, prec);
-        unpack_spinor(*ctx, b, out_dev, nrhs, prec);
+        launch_K(*ctx, rho, a, out_dev, nrhs, prec);
         ctx->prof_collect();
     });
 }

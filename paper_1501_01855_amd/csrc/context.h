@@ -157,11 +157,9 @@ inline size_t field_bytes(const Geom &g, int prec)
 inline unsigned site_blocks(const Geom &g, int nt = 256) { return (unsigned)((g.V + nt - 1) / nt); }
 
 // ---- entry points implemented in the .hip files (host side) -------------
-// pack / unpack between canonical complex128 [nf][V][12] and packed fields.
-// FP32 / FP16 packing goes through an FP64 staging field: tmp (nf FP64 fields)
-// if given, else the context's workspace.
-void pack_spinor(Context &c, const double *canon, void *packed, int nf, int prec, double2 *tmp = nullptr);
-void unpack_spinor(Context &c, const void *packed, double *canon, int nf, int prec, double2 *tmp = nullptr);
+// pack / unpack between canonical complex128 [nf][V][12] and packed fields
+void pack_spinor(Context &c, const double *canon, void *packed, int nf, int prec);
+void unpack_spinor(Context &c, const void *packed, double *canon, int nf, int prec);
 void convert_spinor(Context &c, const void *src, int sprec, void *dst, int dprec, int nf);
 void pack_gauge(Context &c, const double *canon);
 
@@ -171,9 +169,10 @@ void pack_gauge(Context &c, const double *canon);
 void noalloc_scratch_init(int device);
 void *noalloc_scratch(int device);
 
-// stencil: out = H in / K in; nf fields in packed layout of precision prec
-void launch_hop(Context &c, const void *in, void *out, int nf, int prec);
-void launch_K(Context &c, double rho, const void *in, void *out, int nf, int prec);
+// stencil: out = H in / K in; nf fields, in packed in precision prec, out in
+// the canonical layout
+void launch_hop(Context &c, const void *in, double *out, int nf, int prec);
+void launch_K(Context &c, double rho, const void *in, double *out, int nf, int prec);
 
 // A graph being built from kernel nodes: while Context::rec is set,
 // launch_k() appends each kernel to it (after the previous node) instead of

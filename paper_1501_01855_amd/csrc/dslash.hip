@@ -23,26 +23,44 @@
 namespace ovl {
 
 // ------------------------------------------------------------- layout kernels
-__global__ void k_pack_f64(const double2 *__restrict__ canon, double2 *__restrict__ out, int64_t V)
+// One lane per site: the canonical layout's 192 bytes of a site are consecutive
+// in one lane's twelve accesses, so a wave's accesses cover whole lines over
+// the twelve; conversions to and from FP32 and FP16 happen on the way.
+template <typename ST>
+__global__ __launch_bounds__(256) void k_pack(const double2 *__restrict__ canon, ST *__restrict__ out, int64_t V)
 {
+    using R = typename Planes<ST>::R;
     const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int f = blockIdx.y;
     if (s >= V) return;
-    const double2 *src = canon + (int64_t)f * V * 12 + s * 12;
-    double2 *dst = out + (int64_t)f * V * 12;
+    const double2 *src = canon + ((int64_t)f * V + s) * 12;
+    cplx<R> v[12];
 #pragma unroll
-    for (int c = 0; c < 12; ++c) dst[c * V + s] = src[c];
+    for (int c = 0; c < 12; ++c) {
+        const double2 t = src[c];
+        v[c] = {(R)t.x, (R)t.y};
+    }
+    st_sp(out + f * fstride<ST>(V), V, s, v);
 }
 
-__global__ void k_unpack_f64(const double2 *__restrict__ in, double2 *__restrict__ canon, int64_t V)
+// Components c0 .. c0 + n - 1 of site s, in the canonical layout.
+template <typename R>
+__device__ __forceinline__ void st_canon(double2 *__restrict__ canon, int64_t s, int c0, int n, const cplx<R> *v)
+{
+    double2 *dst = canon + s * 12 + c0;
+#pragma unroll
+    for (int c = 0; c < n; ++c) dst[c] = make_double2((double)v[c].re, (double)v[c].im);
+}
+
+template <typename ST>
+__global__ __launch_bounds__(256) void k_unpack(const ST *__restrict__ in, double2 *__restrict__ canon, int64_t V)
 {
     const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int f = blockIdx.y;
     if (s >= V) return;
-    const double2 *src = in + (int64_t)f * V * 12;
-    double2 *dst = canon + (int64_t)f * V * 12 + s * 12;
-#pragma unroll
-    for (int c = 0; c < 12; ++c) dst[c] = src[c * V + s];
+    cplx<typename Planes<ST>::R> v[12];
+    ld_sp(in + f * fstride<ST>(V), V, s, v);
+    st_canon(canon + (int64_t)f * V * 12, s, 0, 12, v);
 }
 
 // packed FP64 <-> packed FP32 (per field)
@@ -145,37 +163,31 @@ __global__ void k_h8_to_f64(const h8 *__restrict__ in, double2 *__restrict__ out
     st_sp(out + (int64_t)f * 12 * V, V, s, w);
 }
 
-void pack_spinor(Context &c, const double *canon, void *packed, int nf, int prec, double2 *tmp)
+void pack_spinor(Context &c, const double *canon, void *packed, int nf, int prec)
 {
     const Geom &g = c.g;
-    dim3 grid(site_blocks(g), nf);
-    if (prec != OVL_F64 && tmp == nullptr) tmp = (double2 *)c.buf("pack_tmp", field_bytes(g, OVL_F64) * nf);
-    if (prec == OVL_F64) {
-        k_pack_f64<<<grid, 256, 0, c.stream>>>((const double2 *)canon, (double2 *)packed, g.V);
-    } else if (prec == OVL_F32) {
-        k_pack_f64<<<grid, 256, 0, c.stream>>>((const double2 *)canon, tmp, g.V);
-        k_f64_to_f32<<<grid, 256, 0, c.stream>>>(tmp, (float4 *)packed, g.V);
-    } else {
-        k_pack_f64<<<grid, 256, 0, c.stream>>>((const double2 *)canon, tmp, g.V);
-        k_f64_to_h8<<<grid, 256, 0, c.stream>>>(tmp, (h8 *)packed, g.V);
-    }
+    const dim3 grid(site_blocks(g), nf);
+    const double2 *in = (const double2 *)canon;
+    if (prec == OVL_F64)
+        k_pack<<<grid, 256, 0, c.stream>>>(in, (double2 *)packed, g.V);
+    else if (prec == OVL_F32)
+        k_pack<<<grid, 256, 0, c.stream>>>(in, (float4 *)packed, g.V);
+    else
+        k_pack<<<grid, 256, 0, c.stream>>>(in, (h8 *)packed, g.V);
     OVL_HIP(hipGetLastError());
 }
 
-void unpack_spinor(Context &c, const void *packed, double *canon, int nf, int prec, double2 *tmp)
+void unpack_spinor(Context &c, const void *packed, double *canon, int nf, int prec)
 {
     const Geom &g = c.g;
-    dim3 grid(site_blocks(g), nf);
-    if (prec != OVL_F64 && tmp == nullptr) tmp = (double2 *)c.buf("pack_tmp", field_bytes(g, OVL_F64) * nf);
-    if (prec == OVL_F64) {
-        k_unpack_f64<<<grid, 256, 0, c.stream>>>((const double2 *)packed, (double2 *)canon, g.V);
-    } else if (prec == OVL_F32) {
-        k_f32_to_f64<<<grid, 256, 0, c.stream>>>((const float4 *)packed, tmp, g.V);
-        k_unpack_f64<<<grid, 256, 0, c.stream>>>(tmp, (double2 *)canon, g.V);
-    } else {
-        k_h8_to_f64<<<grid, 256, 0, c.stream>>>((const h8 *)packed, tmp, g.V);
-        k_unpack_f64<<<grid, 256, 0, c.stream>>>(tmp, (double2 *)canon, g.V);
-    }
+    const dim3 grid(site_blocks(g), nf);
+    double2 *out = (double2 *)canon;
+    if (prec == OVL_F64)
+        k_unpack<<<grid, 256, 0, c.stream>>>((const double2 *)packed, out, g.V);
+    else if (prec == OVL_F32)
+        k_unpack<<<grid, 256, 0, c.stream>>>((const float4 *)packed, out, g.V);
+    else
+        k_unpack<<<grid, 256, 0, c.stream>>>((const h8 *)packed, out, g.V);
     OVL_HIP(hipGetLastError());
 }
 
@@ -483,6 +495,29 @@ __device__ __forceinline__ void exchange_halves(cplx<R> acc[12], int half)
     if constexpr (REUSE) __syncthreads();
 }
 
+// Store a finished site (this lane's NC components) to the packed field, or for
+// H and K on request straight to the canonical layout, with the values the
+// packed field would hold: the entry points for H and K return that layout, and
+// unpacking it in a pass of its own writes and reads the field once more
+// (H on twelve FP64 fields of 24^3 x 48, with the packing of the input: 2.66 ms
+// with that pass, 2.08 ms without; K on one FP32 field of 32^3 x 64, where
+// packing and unpacking also went through an FP64 field: 0.90 and 0.51 ms).
+template <typename ST, int EPI, int TPS, typename R>
+__device__ __forceinline__ void store_site(const StencilArgs<ST> &a, unsigned f, int64_t s, int half, cplx<R> *o)
+{
+    constexpr int NC = 12 / TPS;
+    const int64_t V = a.g.V;
+    if constexpr (EPI == EPI_HOP || EPI == EPI_K) {
+        if (a.canon != nullptr) {
+            as_stored(a.out, o, NC);
+            st_canon(a.canon + (int64_t)f * V * 12, s, NC * half, NC, o);
+            return;
+        }
+    }
+    ST *out = a.out + f * fstride<ST>(V);
+    if constexpr (TPS == 1) st_sp(out, V, s, o); else st_sp_half(out, V, s, half, o);
+}
+
 // Finish site s from the hopping sum acc (this lane's NC components) and store
 // it; K2DOT adds its three dot products to part[0..3).
 // OWN: the site's own input spinor is passed in own (one lane per site)
@@ -497,10 +532,7 @@ __device__ __forceinline__ void stencil_epilogue(const StencilArgs<ST> &a, unsig
     cplx<R> o[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) o[c] = acc[c];
-    ST *out = a.out + f * fstride<ST>(V);
-    if constexpr (EPI == EPI_HOP) {
-        if constexpr (TPS == 1) st_sp(out, V, s, o); else st_sp_half(out, V, s, half, o);
-    } else {
+    if constexpr (EPI != EPI_HOP) {
         // D_W psi = (4 - rho) psi - H psi / 2, then gamma_5 (negate spins 2, 3)
         cplx<R> x[NC];
         if constexpr (OWN) {
@@ -548,8 +580,8 @@ __device__ __forceinline__ void stencil_epilogue(const StencilArgs<ST> &a, unsig
                 for (int c = 0; c < NC; ++c) o[c] = o[c] + x[c];
             }
         }
-        if constexpr (TPS == 1) st_sp(out, V, s, o); else st_sp_half(out, V, s, half, o);
     }
+    store_site<ST, EPI, TPS>(a, f, s, half, o);
 }
 
 // The epilogue for FP16 storage with two lanes per site: the lanes of a site
@@ -605,6 +637,13 @@ __device__ __forceinline__ void stencil_epilogue_pair_h8(const StencilArgs<h8> &
         part[0] += (double)d0;
         part[1] += (double)d1;
         part[2] += (double)d2;
+    }
+    if constexpr (EPI == EPI_HOP || EPI == EPI_K) {
+        if (a.canon != nullptr) {
+            as_stored_scaled(o, m);
+            st_canon(a.canon + (int64_t)f * V * 12, s, 6 * half, 6, o);
+            return;
+        }
     }
     st_sp_half_scaled(out, V, s, half, o, m);
 }
@@ -1343,7 +1382,19 @@ __device__ __forceinline__ void ld_pair(const h8 *p, int64_t V, int64_t s, int h
     v[0] = {a.x * sc, a.y * sc};
     v[1] = {b.x * sc, b.y * sc};
 }
-// Store them; v takes the values as stored (m: the site's scale, FP16 only).
+// The values a pair takes once stored (m: the site's scale, FP16 only).
+__device__ __forceinline__ void pair_as_stored(const double2 *, cplx<double> *, float) {}
+__device__ __forceinline__ void pair_as_stored(const float4 *, cplx<float> *, float) {}
+__device__ __forceinline__ void pair_as_stored(const h8 *, cplx<float> v[2], float m)
+{
+    const float inv = h8_inv_scale(m);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const float2 a = h2f2(f22h2(v[c].re * inv, v[c].im * inv));
+        v[c] = {a.x * m, a.y * m};
+    }
+}
+// Store them; v takes the values as stored.
 __device__ __forceinline__ void st_pair(double2 *p, int64_t V, int64_t s, int h, cplx<double> v[2], float)
 {
 #pragma unroll
@@ -1458,6 +1509,15 @@ __global__ __launch_bounds__(D8_NT) void k_stencil_d8(StencilArgs<ST> a, const G
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < 6; ++q) m = fmaxf(m, valid ? mx[q][j] : 0.f);
+    }
+    if constexpr (EPI == EPI_HOP || EPI == EPI_K) {
+        if (a.canon != nullptr) {
+            if (mine) {
+                pair_as_stored(a.out, o, m);
+                st_canon(a.canon + (int64_t)f * V * 12, s, 2 * w, 2, o);
+            }
+            return;
+        }
     }
     if (mine) st_pair(a.out + f * fstride<ST>(V), V, s, w, o, m);
     if constexpr (EPI == EPI_K2DOT) {
@@ -1674,6 +1734,7 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     // are timed one by one, by events attached to the dispatches.
     StencilArgs<ST> t = a;
     t.stop = nullptr;
+    t.canon = nullptr;   // the packed store, whatever the call wants: one choice per key
     t.out = (ST *)c.buf("tune_out", field_bytes(c.g, prec) * nf);
     t.partial = (double *)c.buf("tune_part", sizeof(double) * 3 * (size_t)nf * stencil_tiles_max(c.g));
     constexpr int REPS = 5;
@@ -1760,23 +1821,23 @@ static void stencil_epi(Context &c, int epi, const StencilArgs<ST> &a, const GT 
 
 void stencil(Context &c, int epi, int prec, const void *in, void *out, int nf, double rho,
              double sigma, const void *aux, double *partial, const int *stop, int it, const void *aux2,
-             const int *itb)
+             const int *itb, double2 *canon)
 {
     OVL_REQUIRE(c.have_gauge, OVL_ERR_STATE, "no gauge field loaded");
     if (prec == OVL_F64) {
         StencilArgs<double2> a{c.g, (const double2 *)in, (double2 *)out, (const double2 *)aux,
-                               (const double2 *)aux2, 4.0 - rho, sigma, partial, stop, it, itb};
+                               (const double2 *)aux2, 4.0 - rho, sigma, partial, stop, it, itb, canon};
         stencil_epi(c, epi, a, c.U64, nf, prec);
     } else if (prec == OVL_F32) {
         StencilArgs<float4> a{c.g, (const float4 *)in, (float4 *)out, (const float4 *)aux,
-                              (const float4 *)aux2, 4.0 - rho, sigma, partial, stop, it, itb};
+                              (const float4 *)aux2, 4.0 - rho, sigma, partial, stop, it, itb, canon};
         if (c.g.two_row)
             stencil_epi(c, epi, a, (const f2r12 *)c.U32r, nf, prec);
         else
             stencil_epi(c, epi, a, (const float2 *)c.U32, nf, prec);
     } else {
         StencilArgs<h8> a{c.g, (const h8 *)in, (h8 *)out, (const h8 *)aux, (const h8 *)aux2, 4.0 - rho,
-                          sigma, partial, stop, it, itb};
+                          sigma, partial, stop, it, itb, canon};
         if (c.g.two_row)
             stencil_epi(c, epi, a, (const h2r12 *)c.U16r, nf, prec);
         else
@@ -1801,14 +1862,14 @@ int stencil_variant(Context &c, int epi, int prec, int nf)
     return it == c.tuned.end() ? -1 : it->second;
 }
 
-void launch_hop(Context &c, const void *in, void *out, int nf, int prec)
+void launch_hop(Context &c, const void *in, double *out, int nf, int prec)
 {
-    stencil(c, EPI_HOP, prec, in, out, nf, 0.0, 0.0, nullptr, nullptr);
+    stencil(c, EPI_HOP, prec, in, nullptr, nf, 0.0, 0.0, nullptr, nullptr, nullptr, 0, nullptr, nullptr, (double2 *)out);
 }
 
-void launch_K(Context &c, double rho, const void *in, void *out, int nf, int prec)
+void launch_K(Context &c, double rho, const void *in, double *out, int nf, int prec)
 {
-    stencil(c, EPI_K, prec, in, out, nf, rho, 0.0, nullptr, nullptr);
+    stencil(c, EPI_K, prec, in, nullptr, nf, rho, 0.0, nullptr, nullptr, nullptr, 0, nullptr, nullptr, (double2 *)out);
 }
 
 // Algorithmic HBM bytes of one stencil launch per field (perfect neighbour

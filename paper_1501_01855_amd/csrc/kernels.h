@@ -24,6 +24,7 @@ struct StencilArgs {
     const int *stop; // per-field: skip when it >= stop[f] (nullable)
     int it;          // iteration, or its offset from *itb when itb is set
     const int *itb = nullptr;   // device iteration base (graph replays)
+    double2 *canon = nullptr;   // EPI_HOP, EPI_K: store here, in the canonical layout, instead of out
 };
 
 // w = K t + s0 p with the partials (p, w), Re (r, w) and (w, w) of every tile
@@ -36,7 +37,7 @@ int stencil_k2_dot(Context &c, int prec, const void *t, void *w, int nf, double 
 
 void stencil(Context &c, int epi, int prec, const void *in, void *out, int nf, double rho,
              double sigma, const void *aux, double *partial, const int *stop = nullptr, int it = 0,
-             const void *aux2 = nullptr, const int *itb = nullptr);
+             const void *aux2 = nullptr, const int *itb = nullptr, double2 *canon = nullptr);
 // algorithmic bytes of one field's stencil (spinors and links), and of the
 // links alone (read once by a launch over several fields)
 double stencil_bytes(const Geom &g, int prec, int epi);
