@@ -15,8 +15,17 @@
 // The lower half of (1 -+ gamma_mu) psi is a unitary image of the upper one,
 // so the two-spin sum equals the four-spin contraction of the definition.
 //
-// Cost: two multi-shift solves that keep every shifted solution, 2 N_Z kernel
-// applications and one pass of the force kernel below.
+// Cost: one multi-shift solve over both sources (psi and K chi'), which keeps
+// every shifted solution, 2 N_Z kernel applications and one pass of the force
+// kernel below.  With both derivatives wanted, dS/dpsi comes from the same
+// solutions, eps(K) chi' = sum_l omega_l b_l, so that its sign call (another
+// multi-shift solve) falls away.  Both derivatives took 14.0 ms on 8^3 x 16 in
+// FP64 and 335 ms on 32^3 x 64 in FP32 with three solves one after another
+// (their shift vectors updated in every iteration), and take 3.4 and 123 ms.
+#include <algorithm>
+#include <cmath>
+#include <vector>
+
 #include "context.h"
 #include "fields.h"
 #include "kernels.h"
@@ -149,32 +158,107 @@ __global__ __launch_bounds__(256) void k_link_force(const ST *__restrict__ chip,
     force_dir<3>(chip, a, b, ka, kb, lstride, k, nz, V, s, sf[3], G, accumulate != 0);
 }
 
+// dpsi = (1 + mu)/2 chi + (1 - mu)/2 sum_l omega_l b_l, that is gamma_5 D chi'
+// (gamma_5 chi' = chi): the sum in the solutions' precision, as the multi-shift
+// CG forms its own sums, 16 bytes of a field per lane.
+struct PoleCoef {
+    double w[NZMAX];
+};
 template <typename ST>
-static void link_force_t(Context &c, double rho, double mu, const ovl_zolo &z, const void *psi, const void *chip,
-                         double2 *dU, int nf, double eta, int prec, int maxiter, ovl_stats *st)
+__global__ __launch_bounds__(256) void k_psi_gradient(const ST *__restrict__ b, int64_t lstride, PoleCoef k, int nz,
+                                                      const double2 *__restrict__ chip, double2 *__restrict__ dpsi,
+                                                      double cc, double cs, int64_t V)
+{
+    using R = typename Planes<ST>::R;
+    constexpr int PL = Planes<ST>::n, NC = 12 / PL;   // planes, complex numbers per plane
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= PL * V) return;
+    const int f = blockIdx.y;
+    const int64_t s = i % V;
+    const int q = (int)(i / V);   // plane
+    const ST *bf = b + f * fstride<ST>(V) + i;
+    R acc[2 * NC];
+#pragma unroll
+    for (int c = 0; c < 2 * NC; ++c) acc[c] = R(0);
+    for (int l = 0; l < nz; ++l) {
+        const ST t = bf[l * lstride];
+        const R w = (R)k.w[l];
+        const R *tr = reinterpret_cast<const R *>(&t);
+#pragma unroll
+        for (int c = 0; c < 2 * NC; ++c) acc[c] += w * tr[c];
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int64_t o = (int64_t)f * 12 * V + (q * NC + c) * V + s;
+        const double g = q * NC + c < 6 ? cc : -cc;   // chi = gamma_5 chi'
+        const double2 x = chip[o];
+        dpsi[o] = make_double2(g * x.x + cs * (double)acc[2 * c], g * x.y + cs * (double)acc[2 * c + 1]);
+    }
+}
+
+// The link gradient into dU and, with dpsi, dS/dpsi; src holds psi (nf fields)
+// and room for as many sources K chi' after it.
+template <typename ST>
+static void link_force_t(Context &c, double rho, double mu, const ovl_zolo &z, ST *src, const void *chip,
+                         const double2 *chip64, double2 *dpsi, double2 *dU, int nf, double eta, int prec, int maxiter,
+                         ovl_stats *st)
 {
     const Geom &g = c.g;
     const int nz = z.n_z;
     const size_t FB = field_bytes(g, prec);
     const int64_t fs = fstride<ST>(g.V);   // elements of ST per field
-    ST *t = (ST *)c.buf("adj_t", FB * nf);
-    ST *xa = (ST *)c.buf("adj_xa", FB * nf * nz);
-    ST *xb = (ST *)c.buf("adj_xb", FB * nf * nz);
-    ST *ka = (ST *)c.buf("adj_ka", FB * nf * nz);
-    ST *kb = (ST *)c.buf("adj_kb", FB * nf * nz);
-    std::vector<double> e(nf, eta);
-    stencil(c, EPI_K, prec, chip, t, nf, rho, 0.0, nullptr, nullptr);   // K chi'
-    shifts_mscg(c, rho, z, psi, xa, nf, e.data(), prec, maxiter, st);   // a_l = X_l psi
-    shifts_mscg(c, rho, z, t, xb, nf, e.data(), prec, maxiter, st);     // b_l = X_l K chi'
-    stencil(c, EPI_K, prec, xa, ka, nf * nz, rho, 0.0, nullptr, nullptr);
-    stencil(c, EPI_K, prec, xb, kb, nf * nz, rho, 0.0, nullptr, nullptr);
+    const size_t half_bytes = FB * nf * nz;
+    ST *x = (ST *)c.buf("adj_x", 2 * half_bytes);    // a_l and b_l
+    ST *kx = (ST *)c.buf("adj_kx", 2 * half_bytes);  // K a_l and K b_l
+    stencil(c, EPI_K, prec, chip, src + nf * fs, nf, rho, 0.0, nullptr, nullptr);   // K chi'
+    // a_l = X_l psi and b_l = X_l K chi', each to |zeta_l| ||r|| <= eta ||source||.
+    // Where sum_l omega_l b_l stands for the sign function its error has to
+    // stay within eta ||chi'||: ||X_l|| <= 1/(sigma_l + a^2) on the interval
+    // [a, b] of |K|, and ||K chi'|| <= (|4 - rho| + 4) ||chi'||, so eta is
+    // scaled by the smallest (sigma_l + a^2)/(omega_l N_Z (|4 - rho| + 4)), as
+    // if every pole erred by its N_Z-th part.
+    double tight = 1.0;
+    if (dpsi)
+        for (int l = 0; l < nz; ++l)
+            tight = std::min(tight, (z.sigma[l] + z.a * z.a) / (z.omega[l] * nz * (std::fabs(4.0 - rho) + 4.0)));
+    std::vector<double> e(2 * nf, eta);
+    for (int f = 0; f < nf; ++f) e[nf + f] = eta * tight;
+    // Both sources in one multi-shift CG (one launch carries both, links read
+    // once), its shift vectors [l][2 nf], while the device has room for twice
+    // as many; else one after the other, [l][nf] each.
+    bool together = true;
+    if (c.pool["ms_p"].bytes < 2 * half_bytes) {
+        size_t avail = 0, total = 0;
+        OVL_HIP(hipMemGetInfo(&avail, &total));
+        together = 2 * half_bytes + 16 * FB * nf <= avail / 2;
+    }
+    if (together) {
+        shifts_mscg(c, rho, z, src, x, 2 * nf, e.data(), prec, maxiter, st);
+    } else {
+        shifts_mscg(c, rho, z, src, x, nf, e.data(), prec, maxiter, st);
+        shifts_mscg(c, rho, z, src + nf * fs, x + (int64_t)nf * nz * fs, nf, e.data() + nf, prec, maxiter, st);
+    }
+    const int half = nf * nz;
+    for (int h = 0; h < 2; ++h)   // two launches: the launch shapes are timed on half the fields
+        stencil(c, EPI_K, prec, x + (int64_t)h * half * fs, kx + (int64_t)h * half * fs, half, rho, 0.0, nullptr,
+                nullptr);
     if (st) st->dslash_calls[prec] += nf * (1 + 2 * nz);
+    const int64_t lstride = (int64_t)(together ? 2 : 1) * nf * fs;
+    const int64_t to_b = (int64_t)(together ? nf : half) * fs;
+    const ST *xb = x + to_b, *kb = kx + to_b;
+    if (dpsi) {
+        PoleCoef w{};
+        for (int l = 0; l < nz; ++l) w.w[l] = z.omega[l];
+        const int64_t n = (int64_t)Planes<ST>::n * g.V;
+        k_psi_gradient<ST><<<dim3((unsigned)((n + 255) / 256), nf), 256, 0, c.stream>>>(
+            xb, lstride, w, nz, chip64, dpsi, 0.5 * (1.0 + mu), 0.5 * (1.0 - mu), g.V);
+        OVL_HIP(hipGetLastError());
+    }
     ForceCoef k{};
     for (int l = 0; l < nz; ++l) k.w[l] = -0.25 * (1.0 - mu) * z.omega[l];
-    const int64_t lstride = (int64_t)nf * fs;
     for (int f = 0; f < nf; ++f) {
         const int64_t o = (int64_t)f * fs;
-        k_link_force<ST><<<site_blocks(g), 256, 0, c.stream>>>((const ST *)chip + o, xa + o, xb + o, ka + o, kb + o,
+        k_link_force<ST><<<site_blocks(g), 256, 0, c.stream>>>((const ST *)chip + o, x + o, xb + o, kx + o, kb + o,
                                                               lstride, k, nz, g, dU, f > 0);
         OVL_HIP(hipGetLastError());
     }
@@ -190,20 +274,20 @@ void overlap_adjoint(Context &c, double rho, double mu, const ovl_zolo &z, const
     double2 *chip = (double2 *)c.buf("adj_chip", FB64);
     copy_fields(c, chi, chip, nf, OVL_F64);
     gamma5_f64(c, chip, nf);   // chi' = gamma_5 chi
-    if (dpsi) {                // D^dagger chi = gamma_5 D chi'
+    if (!dU) {                 // D^dagger chi = gamma_5 D chi'
         overlap_f64(c, rho, mu, z, chip, dpsi, nf, eta, prec, maxiter, st);
         gamma5_f64(c, dpsi, nf);
+        return;
     }
-    if (!dU) return;
+    const size_t FB = field_bytes(c.g, prec) * nf;
+    void *src = c.buf("adj_src", 2 * FB);
+    convert_spinor(c, psi, OVL_F64, src, prec, nf);
     if (prec == OVL_F64) {
-        link_force_t<double2>(c, rho, mu, z, psi, chip, dU, nf, eta, prec, maxiter, st);
+        link_force_t<double2>(c, rho, mu, z, (double2 *)src, chip, chip, dpsi, dU, nf, eta, prec, maxiter, st);
     } else {
-        const size_t FB = field_bytes(c.g, prec) * nf;
-        void *p32 = c.buf("adj_psi32", FB);
         void *c32 = c.buf("adj_chi32", FB);
-        convert_spinor(c, psi, OVL_F64, p32, prec, nf);
         convert_spinor(c, chip, OVL_F64, c32, prec, nf);
-        link_force_t<float4>(c, rho, mu, z, p32, c32, dU, nf, eta, prec, maxiter, st);
+        link_force_t<float4>(c, rho, mu, z, (float4 *)src, c32, chip, dpsi, dU, nf, eta, prec, maxiter, st);
     }
 }
 
