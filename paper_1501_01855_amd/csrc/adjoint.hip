@@ -129,33 +129,34 @@ __device__ __forceinline__ void force_dir(const ST *chip, const ST *a, const ST 
     }
 }
 
-// One thread per site, all four link directions; G canonical [V][4][3][3].
+// 64 sites per block, one wave per link direction; G canonical [V][4][3][3].
 // Field arguments point at the field of one right-hand side; shift l of
-// a, b, ka, kb is lstride elements further on.
+// a, b, ka, kb is lstride elements further on.  Bound by the loads: each pole
+// brings four spinors of the site and four of each neighbour, and the waves of
+// a block find the site's own in cache.  With one lane walking the four
+// directions there were a quarter of the waves, one per SIMD: 436 against 86 us
+// on 8^3 x 16 in FP64, 19.4 against 11.5 ms on 32^3 x 64 in FP32 (20 poles).
 template <typename ST>
-__global__ __launch_bounds__(256) void k_link_force(const ST *__restrict__ chip, const ST *__restrict__ a,
-                                                    const ST *__restrict__ b, const ST *__restrict__ ka,
-                                                    const ST *__restrict__ kb, int64_t lstride, ForceCoef k, int nz,
-                                                    Geom g, double2 *__restrict__ G, int accumulate)
+__global__ __launch_bounds__(256, 2) void k_link_force(const ST *__restrict__ chip, const ST *__restrict__ a,
+                                                       const ST *__restrict__ b, const ST *__restrict__ ka,
+                                                       const ST *__restrict__ kb, int64_t lstride, ForceCoef k, int nz,
+                                                       Geom g, double2 *__restrict__ G, int accumulate)
 {
     const int64_t V = g.V;
-    const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    unsigned tile, field;
+    tile_of_block<true>(tile, field);
+    const int64_t s = (int64_t)tile * 64 + (threadIdx.x & 63);
     if (s >= V) return;
-    int32_t co[4];
-    int64_t r = s;
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-        co[m] = (int32_t)(r % g.L[m]);
-        r /= g.L[m];
+    const int mu = threadIdx.x >> 6;
+    const int64_t st = g.stride[mu];
+    const int32_t Lm = g.L[mu], co = (int32_t)((s / st) % Lm);
+    const int64_t sf = co + 1 == Lm ? s - (int64_t)(Lm - 1) * st : s + st;
+    switch (mu) {
+    case 0: force_dir<0>(chip, a, b, ka, kb, lstride, k, nz, V, s, sf, G, accumulate != 0); break;
+    case 1: force_dir<1>(chip, a, b, ka, kb, lstride, k, nz, V, s, sf, G, accumulate != 0); break;
+    case 2: force_dir<2>(chip, a, b, ka, kb, lstride, k, nz, V, s, sf, G, accumulate != 0); break;
+    default: force_dir<3>(chip, a, b, ka, kb, lstride, k, nz, V, s, sf, G, accumulate != 0); break;
     }
-    co[3] = (int32_t)r;
-    int64_t sf[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) sf[m] = co[m] + 1 == g.L[m] ? s - (int64_t)(g.L[m] - 1) * g.stride[m] : s + g.stride[m];
-    force_dir<0>(chip, a, b, ka, kb, lstride, k, nz, V, s, sf[0], G, accumulate != 0);
-    force_dir<1>(chip, a, b, ka, kb, lstride, k, nz, V, s, sf[1], G, accumulate != 0);
-    force_dir<2>(chip, a, b, ka, kb, lstride, k, nz, V, s, sf[2], G, accumulate != 0);
-    force_dir<3>(chip, a, b, ka, kb, lstride, k, nz, V, s, sf[3], G, accumulate != 0);
 }
 
 // dpsi = (1 + mu)/2 chi + (1 - mu)/2 sum_l omega_l b_l, that is gamma_5 D chi'
@@ -258,7 +259,7 @@ static void link_force_t(Context &c, double rho, double mu, const ovl_zolo &z, S
     for (int l = 0; l < nz; ++l) k.w[l] = -0.25 * (1.0 - mu) * z.omega[l];
     for (int f = 0; f < nf; ++f) {
         const int64_t o = (int64_t)f * fs;
-        k_link_force<ST><<<site_blocks(g), 256, 0, c.stream>>>((const ST *)chip + o, x + o, xb + o, kx + o, kb + o,
+        k_link_force<ST><<<site_blocks(g, 64), 256, 0, c.stream>>>((const ST *)chip + o, x + o, xb + o, kx + o, kb + o,
                                                               lstride, k, nz, g, dU, f > 0);
         OVL_HIP(hipGetLastError());
     }
