@@ -179,6 +179,7 @@ Context::~Context()
     for (auto &kv : pool)
         if (kv.second.p) hipFree(kv.second.p);
     if (U64) hipFree(U64);
+    if (U64r) hipFree(U64r);
     if (U32) hipFree(U32);
     if (U16) hipFree(U16);
     if (U32r) hipFree(U32r);

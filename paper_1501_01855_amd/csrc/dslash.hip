@@ -92,10 +92,29 @@ __global__ void k_f32_to_f64(const float4 *__restrict__ in, double2 *__restrict_
 
 __global__ void k_pack_gauge(const double2 *__restrict__ canon, double2 *__restrict__ U64,
                              float2 *__restrict__ U32, __half2 *__restrict__ U16, float2 *__restrict__ U32r,
-                             __half2 *__restrict__ U16r, int64_t V, int64_t Pu)
+                             __half2 *__restrict__ U16r, double2 *__restrict__ U64r, int64_t V, int64_t Pu)
 {
     const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (s >= V) return;
+    // FP64 two-row form (the planes ld_link reads for d2r12); a difference that
+    // does not fit is stored as infinity, but such links use the full form
+    for (int mu = 0; mu < 4; ++mu) {
+        cplx<double> u[9];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const double2 t = canon[s * 36 + mu * 9 + k];
+            U64r[(mu * 6 + k) * Pu + s] = t;
+            u[k] = {t.x, t.y};
+        }
+        third_row_d(u);
+        ThirdDiff d;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double2 t = canon[s * 36 + mu * 9 + 6 + k];
+            d.h[k] = f22h2((float)((t.x - u[6 + k].re) / THIRD_UNIT), (float)((t.y - u[6 + k].im) / THIRD_UNIT));
+        }
+        reinterpret_cast<ThirdDiff *>(U64r + 24 * Pu)[mu * Pu + s] = d;
+    }
     // two-row forms (the planes ld_link reads for f2r12 / h2r12): entries
     // 0..3 in the Q planes, 4 and 5 in the R plane
     for (int mu = 0; mu < 4; ++mu)
@@ -244,20 +263,27 @@ __global__ __launch_bounds__(256) void k_su3_dev(const double2 *__restrict__ can
 // Links whose third rows agree with the two-row rebuild to this bound use
 // the two-row form in FP32 and FP16 (about the rounding of FP32 storage).
 static constexpr double TWO_ROW_TOL = 0x1p-23;
+// ... and to this bound in FP64, where the difference is kept (d2r12): 432
+// instead of 576 bytes of links per site, for some 40 more operations per link,
+// which the memory-bound stencil has to spare.  D[mu] on 24^3 x 48: 72.8 -> 69.0
+// ms; H on twelve fields 2.08 -> 2.01 ms; K on 3 fields of 15 x 9 x 21 x 27
+// 75.6 -> 71.1 us.
+static constexpr double TWO_ROW_TOL64 = 0x1p-43;
 
 void pack_gauge(Context &c, const double *canon)
 {
     const Geom &g = c.g;
     if (!c.U64) {
         OVL_HIP(hipMalloc(&c.U64, (size_t)g.Pu * 36 * sizeof(double2)));
+        OVL_HIP(hipMalloc(&c.U64r, (size_t)g.Pu * 4 * (6 * sizeof(double2) + sizeof(ThirdDiff))));
         OVL_HIP(hipMalloc(&c.U32, (size_t)g.Pu * 36 * sizeof(float2)));
         OVL_HIP(hipMalloc(&c.U16, (size_t)g.Pu * 36 * sizeof(__half2)));
         OVL_HIP(hipMalloc(&c.U32r, (size_t)g.Pu * 24 * sizeof(float2)));
         OVL_HIP(hipMalloc(&c.U16r, (size_t)g.Pu * 24 * sizeof(__half2)));
-        c.bytes_held += (int64_t)g.Pu * (36 * (16 + 8 + 4) + 24 * (8 + 4));
+        c.bytes_held += (int64_t)g.Pu * (36 * (16 + 8 + 4) + 24 * (8 + 4) + 4 * (6 * 16 + 12));
     }
     k_pack_gauge<<<site_blocks(g), 256, 0, c.stream>>>((const double2 *)canon, c.U64, c.U32, (__half2 *)c.U16,
-                                                       (float2 *)c.U32r, (__half2 *)c.U16r, g.V, g.Pu);
+                                                       (float2 *)c.U32r, (__half2 *)c.U16r, (double2 *)c.U64r, g.V, g.Pu);
     OVL_HIP(hipGetLastError());
     const int nb = (int)site_blocks(g);
     double *part = (double *)c.buf("su3_dev", sizeof(double) * nb);
@@ -276,6 +302,7 @@ void pack_gauge(Context &c, const double *canon)
 void update_link_form(Context &c)
 {
     c.g.two_row = (c.two_row_opt && c.have_gauge && c.su3_dev >= 0.0 && c.su3_dev <= TWO_ROW_TOL) ? 1 : 0;
+    c.g.two_row64 = c.g.two_row && c.su3_dev <= TWO_ROW_TOL64 ? 1 : 0;
 }
 
 // ------------------------------------------------------------- stencil kernel
@@ -1741,7 +1768,7 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     struct Events {
         hipEvent_t e[2 * REPS] = {};
         Events() { for (auto &x : e) OVL_HIP(hipEventCreate(&x)); }
-        ~Events() { for (auto &x : e) if (x) hipEventDestroy(x); }
+        ~Events() { for (auto &x : e) if (x) (void)hipEventDestroy(x); }
     } ev;
     auto single = [&](int v) {   // the fastest launch's own time
         PendingEvent pe{};
@@ -1827,7 +1854,10 @@ void stencil(Context &c, int epi, int prec, const void *in, void *out, int nf, d
     if (prec == OVL_F64) {
         StencilArgs<double2> a{c.g, (const double2 *)in, (double2 *)out, (const double2 *)aux,
                                (const double2 *)aux2, 4.0 - rho, sigma, partial, stop, it, itb, canon};
-        stencil_epi(c, epi, a, c.U64, nf, prec);
+        if (c.g.two_row64)
+            stencil_epi(c, epi, a, (const d2r12 *)c.U64r, nf, prec);
+        else
+            stencil_epi(c, epi, a, (const double2 *)c.U64, nf, prec);
     } else if (prec == OVL_F32) {
         StencilArgs<float4> a{c.g, (const float4 *)in, (float4 *)out, (const float4 *)aux,
                               (const float4 *)aux2, 4.0 - rho, sigma, partial, stop, it, itb, canon};
@@ -1877,6 +1907,7 @@ void launch_K(Context &c, double rho, const void *in, double *out, int nf, int p
 // reads of the epilogues that take more inputs.
 double stencil_link_bytes(const Geom &g, int prec)
 {
+    if (prec == OVL_F64 && g.two_row64) return (double)g.V * 4 * (6 * 16 + 12);
     const int entries = (prec != OVL_F64 && g.two_row) ? 24 : 36;   // complex entries per site
     return (double)g.V * entries * (prec == OVL_F64 ? 16 : prec == OVL_F32 ? 8 : 4);
 }

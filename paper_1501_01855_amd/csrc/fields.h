@@ -346,9 +346,23 @@ struct f2r12 {
 struct h2r12 {
     __half2 v;
 };
+// FP64: two rows and, for the third, its difference from the rebuild in FP16
+// units of 2^-58 (the planes Q [4 mu][6][P] of double2, then R [4 mu][P] of
+// three packed halves): 108 bytes per link instead of 144.  Used where every
+// link's third row is within 2^-43 of the rebuild, so that the difference fits
+// and its rounding, at most 2^-11 of it, is below the rounding of the entries
+// themselves: the stencil sees the loaded links to 2^-54, and to 2^-59 where
+// they are in SU(3) to a few 1e-15.
+struct d2r12 {
+    double2 v;
+};
+struct ThirdDiff {
+    uint32_t h[3];
+};
 template <typename GT>
 struct is_two_row {
-    static constexpr bool value = std::is_same<GT, f2r12>::value || std::is_same<GT, h2r12>::value;
+    static constexpr bool value =
+        std::is_same<GT, f2r12>::value || std::is_same<GT, h2r12>::value || std::is_same<GT, d2r12>::value;
 };
 
 // u[6..8] = conj(u[0..2] x u[3..5]), row-major u[a * 3 + b]
@@ -361,6 +375,41 @@ __device__ __forceinline__ void su3_third_row(cplx<R> u[9])
     u[6] = {c0.re, -c0.im};
     u[7] = {c1.re, -c1.im};
     u[8] = {c2.re, -c2.im};
+}
+
+// The FP64 rebuild, every rounding spelled out: the packing kernel and the
+// stencils must form the same values, whatever the compiler contracts.
+// conj(x y - z w)
+__device__ __forceinline__ cplx<double> conj_cross_d(cplx<double> x, cplx<double> y, cplx<double> z, cplx<double> w)
+{
+    const double re = __builtin_fma(x.re, y.re, __builtin_fma(-x.im, y.im, __builtin_fma(-z.re, w.re, z.im * w.im)));
+    const double im = __builtin_fma(x.re, y.im, __builtin_fma(x.im, y.re, __builtin_fma(-z.re, w.im, -(z.im * w.re))));
+    return {re, -im};
+}
+__device__ __forceinline__ void third_row_d(cplx<double> u[9])
+{
+    u[6] = conj_cross_d(u[1], u[5], u[2], u[4]);
+    u[7] = conj_cross_d(u[2], u[3], u[0], u[5]);
+    u[8] = conj_cross_d(u[0], u[4], u[1], u[3]);
+}
+static constexpr double THIRD_UNIT = 0x1p-58;
+__device__ __forceinline__ void ld_link(const d2r12 *__restrict__ U, int64_t P, int mu, int64_t s, cplx<double> u[9])
+{
+    const double2 *Q = reinterpret_cast<const double2 *>(U);
+    const ThirdDiff *R = reinterpret_cast<const ThirdDiff *>(Q + 24 * P);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const double2 t = Q[(mu * 6 + k) * P + s];
+        u[k] = {t.x, t.y};
+    }
+    const ThirdDiff d = R[mu * P + s];
+    third_row_d(u);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const float2 e = h2f2(d.h[k]);
+        u[6 + k].re = __builtin_fma((double)e.x, THIRD_UNIT, u[6 + k].re);
+        u[6 + k].im = __builtin_fma((double)e.y, THIRD_UNIT, u[6 + k].im);
+    }
 }
 
 __device__ __forceinline__ void ld_link(const f2r12 *__restrict__ U, int64_t P, int mu, int64_t s,

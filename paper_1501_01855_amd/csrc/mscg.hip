@@ -777,8 +777,8 @@ static hipGraphExec_t chunk_graph(Context &c, int prec, int nf, bool all, int ch
 {
     std::string key;
     auto put = [&](const void *d, size_t n) { key.append(reinterpret_cast<const char *>(d), n); };
-    const int head[6] = {prec, nf, all ? 1 : 0, chunk, stencil_variant(c, EPI_K, prec, nf),
-                         stencil_variant(c, EPI_K2DOT, prec, nf)};
+    const int head[7] = {prec, nf, all ? 1 : 0, chunk, stencil_variant(c, EPI_K, prec, nf),
+                         stencil_variant(c, EPI_K2DOT, prec, nf), c.g.two_row + 2 * c.g.two_row64};
     put(head, sizeof(head));
     for (const void *q : ptrs) put(&q, sizeof(q));
     for (double v : vals) put(&v, sizeof(v));
