@@ -18,6 +18,7 @@
 #include <chrono>
 #include <cmath>
 #include <complex>
+#include <type_traits>
 
 #include "context.h"
 #include "fields.h"
@@ -143,8 +144,9 @@ static void sign_f64(Context &c, double rho, const ovl_zolo &zin, const double2 
 // FP64, with each block's partial sums of (x, u) = sum conj(x) u: the
 // widening, gamma_5 and the dot (q~, U q) that follows every application of
 // U in Alg. 2, in one pass over the fields.
+// Without WIDEN only the dot is taken: the SUMR step then reads s itself.
 static constexpr int WD_BLOCKS = 512;   // blocks per field of the fused pass
-template <typename ST>
+template <typename ST, bool WIDEN>
 __global__ __launch_bounds__(256) void k_widen_g5_dot(const ST *__restrict__ in, double2 *__restrict__ u,
                                                       const double2 *__restrict__ x, int64_t V, double *partial)
 {
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(256) void k_widen_g5_dot(const ST *__restrict__ in,
         for (int c = 0; c < 12; ++c) {
             const double sg = c < 6 ? 1.0 : -1.0;   // gamma_5 = diag(1, 1, -1, -1) on the spins
             const double ur = sg * (double)v[c].re, ui = sg * (double)v[c].im;
-            u[o + c * V] = make_double2(ur, ui);
+            if constexpr (WIDEN) u[o + c * V] = make_double2(ur, ui);
             const double2 a = x[o + c * V];
             re += a.x * ur + a.y * ui;
             im += a.x * ui - a.y * ur;
@@ -180,11 +182,15 @@ __global__ __launch_bounds__(256) void k_widen_g5_dot(const ST *__restrict__ in,
 // a field whose middle solve has just restarted at a tight accuracy does not
 // pull the others up to FP32 or FP64.
 // With dx non-null, also (dx_f, u_f) for every field into *dot (an FP32 /
-// FP16 result is widened, gamma_5 applied and the dot taken in one pass).
+// FP16 result is widened, gamma_5 applied and the dot taken in one pass).  With
+// keep as well, an FP32 / FP16 result s may stay where it is: *keep then points
+// to it (valid until the next sign call), u = gamma_5 s is not written.
 static void unitary_f64(Context &c, double rho, const ovl_zolo &z, const double2 *q, double2 *u, int nf,
                         const double *eta, const ovl_solver_params &prm, ovl_stats *st,
-                        const double2 *dx = nullptr, std::vector<std::complex<double>> *dot = nullptr)
+                        const double2 *dx = nullptr, std::vector<std::complex<double>> *dot = nullptr,
+                        const void **keep = nullptr, int *keep_prec = nullptr)
 {
+    if (keep) *keep = nullptr;
     int want[MAXF], present[3] = {0, 0, 0};
     for (int f = 0; f < nf; ++f) {
         want[f] = eta[f] > 0.0 ? prec_for(prm, eta[f]) : -1;
@@ -199,10 +205,19 @@ static void unitary_f64(Context &c, double rho, const ovl_zolo &z, const double2
         if (lo) {
             const int64_t V = c.g.V;
             double *part = (double *)c.buf("u_wdot_part", sizeof(double) * WD_BLOCKS * 2 * nf);
-            if (lp == OVL_F32)
-                k_widen_g5_dot<float4><<<dim3(WD_BLOCKS, nf), 256, 0, c.stream>>>((const float4 *)lo, u, dx, V, part);
-            else
-                k_widen_g5_dot<h8><<<dim3(WD_BLOCKS, nf), 256, 0, c.stream>>>((const h8 *)lo, u, dx, V, part);
+            auto widen = [&](auto *in) {
+                using ST = typename std::remove_const<typename std::remove_pointer<decltype(in)>::type>::type;
+                const dim3 grid(WD_BLOCKS, nf);
+                if (keep)
+                    k_widen_g5_dot<ST, false><<<grid, 256, 0, c.stream>>>(in, u, dx, V, part);
+                else
+                    k_widen_g5_dot<ST, true><<<grid, 256, 0, c.stream>>>(in, u, dx, V, part);
+            };
+            if (lp == OVL_F32) widen((const float4 *)lo); else widen((const h8 *)lo);
+            if (keep) {
+                *keep = lo;
+                *keep_prec = lp;
+            }
             OVL_HIP(hipGetLastError());
             const double *h = sum_partials_host(c, part, WD_BLOCKS, 2 * nf);
             dot->resize(nf);
@@ -256,53 +271,112 @@ void overlap_f64(Context &c, double rho, double mu, const ovl_zolo &z, const dou
     overlap_impl(c, rho, mu, z, in, out, nf, e.data(), prec, maxiter, st, false);
 }
 
-// One fused SUMR vector step per field (the vector statements of Alg. 2, in order):
+// The vector statements of Alg. 2, in order:
 //   omega_old = omega; omega = alpha p + kappa (q_old - omega)
 //   p = p + lambda (q_old - omega_old)
 //   x = x + eta (q - omega)
 //   q_old = q; q = (gamma q_t + u)/sigma; q_t = sigma q_t + conj(gamma) q
-// and ||q_new||^2 per block.  Fields with act[f] = 0 are left untouched.
+// Only q and q_t enter the next application of U, so an iteration does the last
+// line alone (k_sumr_basis: q_t and u read, q and q_t written), into the next
+// slot of a ring of q's, and leaves its coefficients in device memory; once per
+// group of iterations k_sumr_solution applies the others to omega, p and x in
+// registers.  Per iteration this moves four fields and, for groups of four,
+// 2.75, where the statements together moved thirteen: 24^3 x 48, one field,
+// @SUMR@.
+// Fields with act[f] = 0 are left untouched.
 struct SumrCoef {
     double ar[MAXF], ai[MAXF], kr[MAXF], ki[MAXF], lr[MAXF], li[MAXF], er[MAXF], ei[MAXF], gr[MAXF], gi[MAXF],
         sigma[MAXF];
     int act[MAXF];
 };
+constexpr int SUMR_GROUP = 4;
+struct SumrRec {   // one iteration's coefficients of one field
+    double ar, ai, kr, ki, lr, li, er, ei;
+    int act, pad;
+};
 
-__global__ __launch_bounds__(256) void k_sumr_step(SumrCoef k, double2 *__restrict__ x, double2 *__restrict__ p,
-                                                   double2 *__restrict__ om, double2 *__restrict__ qold,
-                                                   double2 *__restrict__ q, double2 *__restrict__ qt,
-                                                   const double2 *__restrict__ u, int64_t n, double *partial)
+// u = gamma_5 s: s in the storage ST of the sign call (one lane per site), or u
+// itself (ST = double2, element by element); and ||q_new||^2 per block.
+template <typename ST>
+__global__ __launch_bounds__(256) void k_sumr_basis(SumrCoef k, SumrRec *rec, double2 *__restrict__ q,
+                                                    double2 *__restrict__ qt, const ST *__restrict__ u, int64_t V,
+                                                    double *partial)
 {
     const int f = blockIdx.y;
     double nn = 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        rec[f] = SumrRec{k.ar[f], k.ai[f], k.kr[f], k.ki[f], k.lr[f], k.li[f], k.er[f], k.ei[f], k.act[f], 0};
     if (k.act[f]) {
-        const cplx<double> alpha{k.ar[f], k.ai[f]}, kappa{k.kr[f], k.ki[f]}, lam{k.lr[f], k.li[f]},
-            eta{k.er[f], k.ei[f]}, gam{k.gr[f], k.gi[f]};
+        const cplx<double> gam{k.gr[f], k.gi[f]};
         const double sg = k.sigma[f], is = 1.0 / sg;
-        const int64_t o = (int64_t)f * n;
-        for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-             i += (int64_t)gridDim.x * blockDim.x) {
-            const int64_t j = o + i;
-            const double2 pv = p[j], ov = om[j], qo = qold[j], qv = q[j], tv = qt[j], uv = u[j], xv = x[j];
-            const cplx<double> P{pv.x, pv.y}, O{ov.x, ov.y}, QO{qo.x, qo.y}, Q{qv.x, qv.y}, T{tv.x, tv.y},
-                U{uv.x, uv.y}, X{xv.x, xv.y};
-            const cplx<double> On = alpha * P + kappa * (QO - O);
-            const cplx<double> Pn = P + lam * (QO - O);
-            const cplx<double> Xn = X + eta * (Q - On);
+        const int64_t o = (int64_t)f * 12 * V, step = (int64_t)gridDim.x * blockDim.x;
+        auto one = [&](int64_t j, cplx<double> U) {
+            const double2 tv = qt[j];
+            const cplx<double> T{tv.x, tv.y};
             const cplx<double> Qn = is * (gam * T + U);
             const cplx<double> Tn = sg * T + cmul_conj(gam, Qn);
-            om[j] = make_double2(On.re, On.im);
-            p[j] = make_double2(Pn.re, Pn.im);
-            x[j] = make_double2(Xn.re, Xn.im);
-            qold[j] = qv;
             q[j] = make_double2(Qn.re, Qn.im);
             qt[j] = make_double2(Tn.re, Tn.im);
             nn += Qn.re * Qn.re + Qn.im * Qn.im;
+        };
+        if constexpr (std::is_same<ST, double2>::value) {
+            for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < 12 * V; i += step) {
+                const double2 uv = u[o + i];
+                one(o + i, {uv.x, uv.y});
+            }
+        } else {
+            for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < V; i += step) {
+                cplx<float> v[12];
+                ld_sp(u + f * fstride<ST>(V), V, i, v);
+#pragma unroll
+                for (int c = 0; c < 12; ++c) {
+                    const double g5 = c < 6 ? 1.0 : -1.0;
+                    one(o + c * V + i, {g5 * (double)v[c].re, g5 * (double)v[c].im});
+                }
+            }
         }
     }
     __shared__ double lds[4];
     const double t = block_sum<256>(nn, lds);
     if (threadIdx.x == 0) partial[(int64_t)f * gridDim.x + blockIdx.x] = t;
+}
+
+// The group's iterations j = 0 .. cnt - 1 (coefficients rec[j][f]) on omega, p
+// and x; iteration j has q_old in ring slot first - 1 + j and q in first + j
+// (modulo slots, n elements per field, nf fields per slot).
+__global__ __launch_bounds__(256) void k_sumr_solution(const SumrRec *__restrict__ rec, int cnt,
+                                                       const double2 *__restrict__ ring, int first, int slots,
+                                                       double2 *__restrict__ om, double2 *__restrict__ p,
+                                                       double2 *__restrict__ x, int64_t n)
+{
+    const int f = blockIdx.y, nf = gridDim.y;
+    bool any = false;
+    for (int j = 0; j < cnt; ++j) any = any || rec[j * nf + f].act != 0;
+    if (!any) return;
+    const int64_t o = (int64_t)f * n, ss = (int64_t)nf * n;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        double2 qv[SUMR_GROUP + 1];
+#pragma unroll
+        for (int j = 0; j <= SUMR_GROUP; ++j)
+            if (j <= cnt) qv[j] = ring[((first - 1 + j + slots) % slots) * ss + o + i];
+        const double2 ov = om[o + i], pv = p[o + i], xv = x[o + i];
+        cplx<double> O{ov.x, ov.y}, P{pv.x, pv.y}, X{xv.x, xv.y};
+#pragma unroll
+        for (int j = 0; j < SUMR_GROUP; ++j) {
+            if (j >= cnt) continue;
+            const SumrRec &r = rec[j * nf + f];
+            if (!r.act) continue;
+            const cplx<double> alpha{r.ar, r.ai}, kappa{r.kr, r.ki}, lam{r.lr, r.li}, eta{r.er, r.ei};
+            const cplx<double> QO{qv[j].x, qv[j].y}, Q{qv[j + 1].x, qv[j + 1].y};
+            const cplx<double> On = alpha * P + kappa * (QO - O);
+            P = P + lam * (QO - O);
+            X = X + eta * (Q - On);
+            O = On;
+        }
+        om[o + i] = make_double2(O.re, O.im);
+        p[o + i] = make_double2(P.re, P.im);
+        x[o + i] = make_double2(X.re, X.im);
+    }
 }
 
 static void norms(Context &c, const double2 *x, int nf, std::vector<double> &out)
@@ -352,12 +426,31 @@ static void sumr(Context &c, const ovl_zolo &z, const ovl_solver_params &prm, do
     double2 *rt = (double2 *)c.buf("s_rt", FB * nf);
     double2 *p = (double2 *)c.buf("s_p", FB * nf);
     double2 *om = (double2 *)c.buf("s_om", FB * nf);
-    double2 *q = (double2 *)c.buf("s_q", FB * nf);
-    double2 *qold = (double2 *)c.buf("s_qold", FB * nf);
     double2 *qt = (double2 *)c.buf("s_qt", FB * nf);
     double2 *u = (double2 *)c.buf("s_u", FB * nf);
     const int64_t n = 12 * c.g.V;
-    const int nblk = 256;
+    const int nblk = 512;
+    // the ring of q's: a group's, the one before it and the one after; smaller
+    // groups where device memory is short
+    int group = SUMR_GROUP;
+    if (c.pool["s_q"].bytes < FB * nf * (group + 2)) {
+        size_t avail = 0, total = 0;
+        OVL_HIP(hipMemGetInfo(&avail, &total));
+        while (group > 1 && FB * nf * (group + 2) > avail / 4) group /= 2;
+    }
+    const int slots = group + 2;
+    double2 *ring = (double2 *)c.buf("s_q", FB * nf * slots);
+    SumrRec *rec = (SumrRec *)c.buf("s_rec", sizeof(SumrRec) * SUMR_GROUP * nf);
+    auto slot = [&](int i) { return ring + (size_t)((i + slots) % slots) * n * nf; };
+    int cur = 1, waiting = 0;   // slot of q, iterations whose omega, p, x are due
+    double2 *q = slot(cur), *qold = slot(cur - 1);
+    auto settle = [&] {
+        if (waiting == 0) return;
+        k_sumr_solution<<<dim3(1024, nf), 256, 0, c.stream>>>(rec, waiting, ring, cur - waiting + slots, slots, om, p, x,
+                                                             n);
+        OVL_HIP(hipGetLastError());
+        waiting = 0;
+    };
     double *part = (double *)c.buf("s_part", sizeof(double) * nblk * nf);
     const double zeta = 1.0;
 
@@ -385,6 +478,7 @@ static void sumr(Context &c, const ovl_zolo &z, const ovl_solver_params &prm, do
             any_init = any_init || init[f];
         }
         if (any_init) {
+            settle();
             std::vector<zc> ca(nf, 0.0), cb(nf, 1.0);
             for (int f = 0; f < nf; ++f)
                 if (init[f]) {
@@ -456,7 +550,9 @@ static void sumr(Context &c, const ovl_zolo &z, const ovl_solver_params &prm, do
         if (nact == 0) break;
         for (int f = 0; f < nf; ++f) eta[f] = F[f].active ? eta_for(F[f]) : 0.0;
         std::vector<zc> g;   // (q~, U q), taken with U q
-        unitary_f64(c, rhoK, z, q, u, nf, eta.data(), prm, st, qt, &g);
+        const void *lo = nullptr;   // U q left in the sign call's precision (collection needs it in FP64)
+        int lp = OVL_F64;
+        unitary_f64(c, rhoK, z, q, u, nf, eta.data(), prm, st, qt, &g, collect ? nullptr : &lo, &lp);
         if (collect)   // Alg. 5: every active field's (q, U q); one field unless collecting as a block
             for (int f = 0; f < nf; ++f)
                 if (F[f].active) eig_collect(c, q + (size_t)f * n, u + (size_t)f * n);
@@ -507,8 +603,19 @@ static void sumr(Context &c, const ovl_zolo &z, const ovl_solver_params &prm, do
             sf.iters += 1;
             if (st) st[f].sumr_iters += 1;
         }
-        k_sumr_step<<<dim3(nblk, nf), 256, 0, c.stream>>>(k, x, p, om, qold, q, qt, u, n, part);
+        const dim3 grid(nblk, nf);
+        SumrRec *now = rec + (size_t)waiting * nf;
+        if (lo && lp == OVL_F32)
+            k_sumr_basis<<<grid, 256, 0, c.stream>>>(k, now, slot(cur + 1), qt, (const float4 *)lo, c.g.V, part);
+        else if (lo)
+            k_sumr_basis<<<grid, 256, 0, c.stream>>>(k, now, slot(cur + 1), qt, (const h8 *)lo, c.g.V, part);
+        else
+            k_sumr_basis<<<grid, 256, 0, c.stream>>>(k, now, slot(cur + 1), qt, (const double2 *)u, c.g.V, part);
         OVL_HIP(hipGetLastError());
+        cur = (cur + 1) % slots;
+        q = slot(cur);
+        qold = slot(cur - 1);
+        if (++waiting == group) settle();
         // ||q|| monitoring (Sec. 2)
         const double *hq = sum_partials_host(c, part, nblk, nf);
         const std::vector<double> qn2(hq, hq + nf);
@@ -522,6 +629,7 @@ static void sumr(Context &c, const ovl_zolo &z, const ovl_solver_params &prm, do
             }
         }
     }
+    settle();
 }
 
 // h_f = H w_f = gamma_5 D[mu] w_f for the fields with eta[f] > 0 (sign
