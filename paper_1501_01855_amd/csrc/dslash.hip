@@ -1751,9 +1751,9 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     if (it != c.tuned.end()) return it->second;
     if (c.no_alloc) return 1;   // timing would need workspace and events: fixed shape, not recorded
     if (c.autotune == 0) return c.tuned[key] = 1;
-    // Time every variant on scratch output: three rounds over the variants
-    // (interleaved, so that clock drift hits them alike), five launches each; a
-    // variant counts with its best round, and is dropped once it is far behind.
+    // Time every variant on scratch output: a first look of two launches each,
+    // then rounds of five launches over those not far behind (interleaved, so
+    // that clock drift hits them alike); a variant counts with its best round.
     // Launches of 15 us or more are timed back to back, as the CG issues them.
     // Shorter ones take less time than the host takes to launch them, so that
     // events around the five would time the host (on 8^3 x 16 in FP16 such a
@@ -1770,16 +1770,16 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
         Events() { for (auto &x : e) OVL_HIP(hipEventCreate(&x)); }
         ~Events() { for (auto &x : e) if (x) (void)hipEventDestroy(x); }
     } ev;
-    auto single = [&](int v) {   // the fastest launch's own time
+    auto single = [&](int v, int reps) {   // the fastest launch's own time (as for REPS launches)
         PendingEvent pe{};
-        for (int r = 0; r < REPS; ++r) {
+        for (int r = 0; r < reps; ++r) {
             pe.a = ev.e[2 * r];
             pe.b = ev.e[2 * r + 1];
             launch_by_id<ST, GT, EPI>(c, v, t, U, nf, &pe);
         }
         OVL_HIP(hipEventSynchronize(pe.b));
         float least = 1e30f;
-        for (int r = 0; r < REPS; ++r) {
+        for (int r = 0; r < reps; ++r) {
             float ms = 0.f;
             OVL_HIP(hipEventElapsedTime(&ms, ev.e[2 * r], ev.e[2 * r + 1]));
             least = std::min(least, ms);
@@ -1800,14 +1800,15 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
         if (stencil_variant_ok(c.g, prec, v)) ids.push_back(v);
     std::vector<float> ms_best(N_VARIANTS, 1e30f);
     for (int v : ids) launch_by_id<ST, GT, EPI>(c, v, t, U, nf);   // warm-up
-    for (int v : ids) ms_best[v] = single(v);
-    const bool small = *std::min_element(ms_best.begin(), ms_best.end()) < REPS * 0.015f;
+    for (int v : ids) ms_best[v] = single(v, 2);
+    const float first = *std::min_element(ms_best.begin(), ms_best.end());
+    const bool small = first < REPS * 0.015f;
     if (!small)
-        for (int v : ids) ms_best[v] = chain(v);
+        for (int v : ids) ms_best[v] = ms_best[v] < 1.6f * first ? chain(v) : 1e30f;
     for (int round = 0; round < 2; ++round) {
         const float lead = *std::min_element(ms_best.begin(), ms_best.end());
         for (int v : ids)
-            if (ms_best[v] < 1.3f * lead) ms_best[v] = std::min(ms_best[v], small ? single(v) : chain(v));
+            if (ms_best[v] < 1.3f * lead) ms_best[v] = std::min(ms_best[v], small ? single(v, REPS) : chain(v));
     }
     int best = ids[0];
     for (int v : ids)
