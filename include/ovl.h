@@ -414,9 +414,9 @@ ovl_status ovl_stream_bench(ovl_context *ctx, int32_t kind, const void *src_dev,
  *                    loaded link passes the SU(3) test of ovl_gauge_info
  *                    (otherwise, or with the option off, the full links).
  *                    The FP64 stencil then reads two rows and the third row's
- *                    difference from the rebuild (to 2^-11 of it), when that is
- *                    at most 2^-43 for every link: the links as loaded, to at
- *                    most 2^-54.
+ *                    distance from the rebuild, in 32 bits per real, where
+ *                    that holds every link exactly as loaded (else the full
+ *                    links).
  *   OVL_OPT_OUTER_PRINTED (default off) the GMRESR outer product c = D u
  *                    (Alg. 3) to the accuracy the algorithm prints,
  *                    ||D u - c|| < eps ||b|| ||u|| / ||r||: the sign function

@@ -83,7 +83,7 @@ struct Geom {
     int32_t col_sites;   // cb[0] cb[1] cb[2]
     int32_t col_ok;
     int32_t two_row;     // FP32 / FP16 stencils read the two-row links (set when the links are loaded)
-    int32_t two_row64;   // FP64 stencils read two rows and the third's difference from its rebuild
+    int32_t two_row64;   // FP64 stencils read two rows and the third's difference from its rebuild (the links exactly)
 };
 
 inline Geom make_geom(const int32_t d[4])

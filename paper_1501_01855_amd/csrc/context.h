@@ -57,12 +57,13 @@ struct Context {
 
     // gauge field, packed per precision
     double2 *U64 = nullptr;   // [4][9][Pu] (Geom::Pu: padded plane stride)
-    void *U64r = nullptr;     // two rows and the third's difference: double2 [4][6][Pu] + ThirdDiff [4][Pu]
+    void *U64r = nullptr;     // two rows and the third's difference: double2 [4][6][Pu] + int2 [4][3][Pu]
     float2 *U32 = nullptr;    // 36 Pu float2: float4 [4][4][Pu] + float2 [4][Pu]
     void *U16 = nullptr;      // 36 Pu __half2: uint4 [4][2][Pu] + uint32 [4][Pu]
     void *U32r = nullptr;     // two-row FP32 links: float4 [4][2][Pu] + float4 [4][Pu]
     void *U16r = nullptr;     // two-row FP16 links: uint4 [4][Pu] + uint2 [4][Pu]
     double su3_dev = -1.0;    // largest |third row - conj(row 0 x row 1)| over the loaded links
+    bool third_fits = false;  // every third row fits the FP64 two-row form exactly
     bool two_row_opt = true;  // OVL_OPT_TWO_ROW_LINKS
     bool have_gauge = false;
 

@@ -96,8 +96,8 @@ __global__ void k_pack_gauge(const double2 *__restrict__ canon, double2 *__restr
 {
     const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (s >= V) return;
-    // FP64 two-row form (the planes ld_link reads for d2r12); a difference that
-    // does not fit is stored as infinity, but such links use the full form
+    // FP64 two-row form (the planes ld_link reads for d2r12); where a difference
+    // does not fit (k_su3_dev tells) the full form is used
     for (int mu = 0; mu < 4; ++mu) {
         cplx<double> u[9];
 #pragma unroll
@@ -107,13 +107,15 @@ __global__ void k_pack_gauge(const double2 *__restrict__ canon, double2 *__restr
             u[k] = {t.x, t.y};
         }
         third_row_d(u);
-        ThirdDiff d;
+        int2 *R = reinterpret_cast<int2 *>(U64r + 24 * Pu);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             const double2 t = canon[s * 36 + mu * 9 + 6 + k];
-            d.h[k] = f22h2((float)((t.x - u[6 + k].re) / THIRD_UNIT), (float)((t.y - u[6 + k].im) / THIRD_UNIT));
+            int2 d;
+            third_diff(t.x, u[6 + k].re, d.x);
+            third_diff(t.y, u[6 + k].im, d.y);
+            R[(mu * 3 + k) * Pu + s] = d;
         }
-        reinterpret_cast<ThirdDiff *>(U64r + 24 * Pu)[mu * Pu + s] = d;
     }
     // two-row forms (the planes ld_link reads for f2r12 / h2r12): entries
     // 0..3 in the Q planes, 4 and 5 in the R plane
@@ -231,13 +233,15 @@ void convert_spinor(Context &c, const void *src, int sprec, void *dst, int dprec
 }
 
 // Per block: the largest |u_2b - conj(u_0 x u_1)_b| over the links of its
-// sites (FP64), the test for the two-row form.
+// sites (FP64), the test for the two-row form in FP32 and FP16; and in
+// part[gridDim.x + block] whether a third row does not fit the FP64 form.
 __global__ __launch_bounds__(256) void k_su3_dev(const double2 *__restrict__ canon, int64_t V,
                                                  double *__restrict__ part)
 {
     __shared__ double red[256];
     const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     double m = 0.0;
+    bool misfit = false;
     if (s < V)
         for (int mu = 0; mu < 4; ++mu) {
             cplx<double> u[9];
@@ -250,24 +254,36 @@ __global__ __launch_bounds__(256) void k_su3_dev(const double2 *__restrict__ can
             su3_third_row(w);
 #pragma unroll
             for (int k = 6; k < 9; ++k) m = fmax(m, fmax(fabs(w[k].re - u[k].re), fabs(w[k].im - u[k].im)));
+            third_row_d(w);
+#pragma unroll
+            for (int k = 6; k < 9; ++k) {
+                int32_t d;
+                misfit = !third_diff(u[k].re, w[k].re, d) || !third_diff(u[k].im, w[k].im, d) || misfit;
+            }
         }
+    misfit = __syncthreads_or(misfit);
     red[threadIdx.x] = m;
     __syncthreads();
     for (int h = 128; h > 0; h >>= 1) {
         if ((int)threadIdx.x < h) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + h]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) {
+        part[blockIdx.x] = red[0];
+        part[gridDim.x + blockIdx.x] = misfit ? 1.0 : 0.0;
+    }
 }
 
 // Links whose third rows agree with the two-row rebuild to this bound use
 // the two-row form in FP32 and FP16 (about the rounding of FP32 storage).
 static constexpr double TWO_ROW_TOL = 0x1p-23;
-// ... and to this bound in FP64, where the difference is kept (d2r12): 432
-// instead of 576 bytes of links per site, for some 40 more operations per link,
-// which the memory-bound stencil has to spare.  D[mu] on 24^3 x 48: 72.8 -> 69.0
-// ms; H on twelve fields 2.08 -> 2.01 ms; K on 3 fields of 15 x 9 x 21 x 27
-// 75.6 -> 71.1 us.
+// ... and to this bound, and with every third row fitting the form, in FP64
+// (d2r12): 480 instead of 576 bytes of links per site, for some 40 more
+// operations per link, which the memory-bound stencil has to spare.  Rows
+// further off do not fit but on the smallest lattices; of links in SU(3) to
+// rounding about one in 3e8 does not.  D[mu] on 24^3 x 48: 72.8 -> 70.7 ms; H
+// on twelve fields 2.08 -> 2.05 ms; K on 3 fields of 15 x 9 x 21 x 27 75.6 ->
+// 73.6 us.
 static constexpr double TWO_ROW_TOL64 = 0x1p-43;
 
 void pack_gauge(Context &c, const double *canon)
@@ -275,26 +291,31 @@ void pack_gauge(Context &c, const double *canon)
     const Geom &g = c.g;
     if (!c.U64) {
         OVL_HIP(hipMalloc(&c.U64, (size_t)g.Pu * 36 * sizeof(double2)));
-        OVL_HIP(hipMalloc(&c.U64r, (size_t)g.Pu * 4 * (6 * sizeof(double2) + sizeof(ThirdDiff))));
+        OVL_HIP(hipMalloc(&c.U64r, (size_t)g.Pu * 4 * (6 * sizeof(double2) + 3 * sizeof(int2))));
         OVL_HIP(hipMalloc(&c.U32, (size_t)g.Pu * 36 * sizeof(float2)));
         OVL_HIP(hipMalloc(&c.U16, (size_t)g.Pu * 36 * sizeof(__half2)));
         OVL_HIP(hipMalloc(&c.U32r, (size_t)g.Pu * 24 * sizeof(float2)));
         OVL_HIP(hipMalloc(&c.U16r, (size_t)g.Pu * 24 * sizeof(__half2)));
-        c.bytes_held += (int64_t)g.Pu * (36 * (16 + 8 + 4) + 24 * (8 + 4) + 4 * (6 * 16 + 12));
+        c.bytes_held += (int64_t)g.Pu * (36 * (16 + 8 + 4) + 24 * (8 + 4) + 4 * (6 * 16 + 3 * 8));
     }
     k_pack_gauge<<<site_blocks(g), 256, 0, c.stream>>>((const double2 *)canon, c.U64, c.U32, (__half2 *)c.U16,
                                                        (float2 *)c.U32r, (__half2 *)c.U16r, (double2 *)c.U64r, g.V, g.Pu);
     OVL_HIP(hipGetLastError());
     const int nb = (int)site_blocks(g);
-    double *part = (double *)c.buf("su3_dev", sizeof(double) * nb);
+    double *part = (double *)c.buf("su3_dev", sizeof(double) * 2 * nb);
     k_su3_dev<<<nb, 256, 0, c.stream>>>((const double2 *)canon, g.V, part);
     OVL_HIP(hipGetLastError());
-    std::vector<double> h(nb);
-    OVL_HIP(hipMemcpyAsync(h.data(), part, sizeof(double) * nb, hipMemcpyDeviceToHost, c.stream));
+    std::vector<double> h(2 * nb);
+    OVL_HIP(hipMemcpyAsync(h.data(), part, sizeof(double) * 2 * nb, hipMemcpyDeviceToHost, c.stream));
     OVL_HIP(hipStreamSynchronize(c.stream));
     double m = 0.0;
-    for (double v : h) m = std::max(m, std::isnan(v) ? INFINITY : v);
+    bool fit = true;
+    for (int i = 0; i < nb; ++i) {
+        m = std::max(m, std::isnan(h[i]) ? INFINITY : h[i]);
+        fit = fit && h[nb + i] == 0.0;
+    }
     c.su3_dev = m;
+    c.third_fits = fit;
     c.have_gauge = true;
     update_link_form(c);
 }
@@ -302,7 +323,7 @@ void pack_gauge(Context &c, const double *canon)
 void update_link_form(Context &c)
 {
     c.g.two_row = (c.two_row_opt && c.have_gauge && c.su3_dev >= 0.0 && c.su3_dev <= TWO_ROW_TOL) ? 1 : 0;
-    c.g.two_row64 = c.g.two_row && c.su3_dev <= TWO_ROW_TOL64 ? 1 : 0;
+    c.g.two_row64 = c.g.two_row && c.third_fits && c.su3_dev <= TWO_ROW_TOL64 ? 1 : 0;
 }
 
 // ------------------------------------------------------------- stencil kernel
@@ -1908,7 +1929,7 @@ void launch_K(Context &c, double rho, const void *in, double *out, int nf, int p
 // reads of the epilogues that take more inputs.
 double stencil_link_bytes(const Geom &g, int prec)
 {
-    if (prec == OVL_F64 && g.two_row64) return (double)g.V * 4 * (6 * 16 + 12);
+    if (prec == OVL_F64 && g.two_row64) return (double)g.V * 4 * (6 * 16 + 3 * 8);
     const int entries = (prec != OVL_F64 && g.two_row) ? 24 : 36;   // complex entries per site
     return (double)g.V * entries * (prec == OVL_F64 ? 16 : prec == OVL_F32 ? 8 : 4);
 }

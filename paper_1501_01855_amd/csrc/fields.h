@@ -346,23 +346,14 @@ struct f2r12 {
 struct h2r12 {
     __half2 v;
 };
-// FP64: two rows and, for the third, its difference from the rebuild in FP16
-// units of 2^-58 (the planes Q [4 mu][6][P] of double2, then R [4 mu][P] of
-// three packed halves): 108 bytes per link instead of 144.  Used where every
-// link's third row is within 2^-43 of the rebuild, so that the difference fits
-// and its rounding, at most 2^-11 of it, is below the rounding of the entries
-// themselves: the stencil sees the loaded links to 2^-54, and to 2^-59 where
-// they are in SU(3) to a few 1e-15.
+// FP64: two rows and, for the third, how far the bit pattern of each real lies
+// from that of its rebuild, as a 32-bit whole number (the planes Q [4 mu][6][P]
+// of double2, then R [4 mu][3][P] of int2): 120 bytes per link instead of 144,
+// and the stencil sees the links exactly as loaded.  A link whose third row is
+// the rebuild to rounding (1e-16) fits while its reals are above some 2^-32 in
+// size; where one real of the field does not fit, the full links are used.
 struct d2r12 {
     double2 v;
-};
-struct ThirdDiff {
-    uint32_t h[3];
-};
-template <typename GT>
-struct is_two_row {
-    static constexpr bool value =
-        std::is_same<GT, f2r12>::value || std::is_same<GT, h2r12>::value || std::is_same<GT, d2r12>::value;
 };
 
 // u[6..8] = conj(u[0..2] x u[3..5]), row-major u[a * 3 + b]
@@ -392,24 +383,32 @@ __device__ __forceinline__ void third_row_d(cplx<double> u[9])
     u[7] = conj_cross_d(u[2], u[3], u[0], u[5]);
     u[8] = conj_cross_d(u[0], u[4], u[1], u[3]);
 }
-static constexpr double THIRD_UNIT = 0x1p-58;
+// d = the distance in bit patterns from the rebuilt real to the loaded one; false if it does not fit
+__device__ __forceinline__ bool third_diff(double loaded, double rebuilt, int32_t &d)
+{
+    const int64_t x = (int64_t)((uint64_t)__double_as_longlong(loaded) - (uint64_t)__double_as_longlong(rebuilt));
+    d = (int32_t)x;
+    return d == x;
+}
+__device__ __forceinline__ double third_real(double rebuilt, int32_t d)
+{
+    return __longlong_as_double((long long)((uint64_t)__double_as_longlong(rebuilt) + (uint64_t)(int64_t)d));
+}
 __device__ __forceinline__ void ld_link(const d2r12 *__restrict__ U, int64_t P, int mu, int64_t s, cplx<double> u[9])
 {
     const double2 *Q = reinterpret_cast<const double2 *>(U);
-    const ThirdDiff *R = reinterpret_cast<const ThirdDiff *>(Q + 24 * P);
+    const int2 *R = reinterpret_cast<const int2 *>(Q + 24 * P);
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         const double2 t = Q[(mu * 6 + k) * P + s];
         u[k] = {t.x, t.y};
     }
-    const ThirdDiff d = R[mu * P + s];
+    int2 d[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) d[k] = R[(mu * 3 + k) * P + s];
     third_row_d(u);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const float2 e = h2f2(d.h[k]);
-        u[6 + k].re = __builtin_fma((double)e.x, THIRD_UNIT, u[6 + k].re);
-        u[6 + k].im = __builtin_fma((double)e.y, THIRD_UNIT, u[6 + k].im);
-    }
+    for (int k = 0; k < 3; ++k) u[6 + k] = {third_real(u[6 + k].re, d[k].x), third_real(u[6 + k].im, d[k].y)};
 }
 
 __device__ __forceinline__ void ld_link(const f2r12 *__restrict__ U, int64_t P, int mu, int64_t s,
