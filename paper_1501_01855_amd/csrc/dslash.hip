@@ -1848,7 +1848,8 @@ static void launch_stencil_t(Context &c, const StencilArgs<ST> &a, const GT *U, 
     // fields; their driver books the bytes of the work actually done
     // nf fields in one launch share one read of the links
     const double G = stencil_link_bytes(c.g, prec);
-    const double bytes = a.stop ? 0.0 : (stencil_bytes(c.g, prec, EPI) - G) * nf + G;
+    double bytes = a.stop ? 0.0 : (stencil_bytes(c.g, prec, EPI) - G) * nf + G;
+    if (a.canon) bytes += (double)(field_bytes(c.g, OVL_F64) - field_bytes(c.g, prec)) * nf;   // stored as complex128
     const bool prof = profile && c.prof && !c.no_alloc;
     if (prof) c.prof_begin(pe, KERN_STENCIL, prec, bytes);
     launch_by_id<ST, GT, EPI>(c, v, a, U, nf, prof ? &pe : nullptr);
@@ -1925,8 +1926,8 @@ void launch_K(Context &c, double rho, const void *in, double *out, int nf, int p
 }
 
 // Algorithmic HBM bytes of one stencil launch per field (perfect neighbour
-// reuse, no index table): read in + links, write out, plus the extra own-site
-// reads of the epilogues that take more inputs.
+// reuse, no index table): read in + links, write out (packed), plus the extra
+// own-site reads of the epilogues that take more inputs.
 double stencil_link_bytes(const Geom &g, int prec)
 {
     if (prec == OVL_F64 && g.two_row64) return (double)g.V * 4 * (6 * 16 + 3 * 8);
