@@ -456,7 +456,10 @@ ovl_status ovl_gauge_info(ovl_context *ctx, double *su3_deviation, int32_t *two_
  * after another, when the x, y, z extents split into 8 columns; 22: eight
  * lanes per site, one for each hop, on lattices of at most 65536 sites).
  * A key is (precision * 8 + epilogue) * 64 + min(field count, 63), the
- * epilogue 0 for the plain hopping term; variants run 0 .. OVL_STENCIL_VARIANTS - 1.
+ * epilogue 0 for the plain hopping term, 1 for K inside the sign function, 4
+ * for K stored for the caller (ovl_kernel_K_apply), 2 and 3 for K with a sum;
+ * each is timed with the store it uses.  A pair for epilogue 1 sets 4 as well
+ * where the table has none for it.  Variants run 0 .. OVL_STENCIL_VARIANTS - 1.
  * ovl_tuning_get copies up to cap (key, variant) pairs and sets *n to the
  * number held; ovl_tuning_set installs pairs (a variant out of range or not
  * admissible on the context's lattice and precision is an argument error),

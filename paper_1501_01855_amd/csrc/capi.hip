@@ -782,7 +782,9 @@ ovl_status ovl_tuning_set(ovl_context *ctx, const int32_t *keys, const int32_t *
             OVL_REQUIRE(keys[i] >= 0 && prec <= OVL_HALF && stencil_variant_ok(ctx->g, prec, variants[i]),
                         OVL_ERR_ARG, "tuning variant out of range for this lattice and precision");
         }
-        for (int i = 0; i < n; ++i) ctx->tuned[keys[i]] = variants[i];
+        for (int i = 0; i < n; ++i)   // a choice for K is one for both of its stores ...
+            if (keys[i] / 64 % 8 == EPI_K) ctx->tuned[keys[i] + (TUNE_K_CANON - EPI_K) * 64] = variants[i];
+        for (int i = 0; i < n; ++i) ctx->tuned[keys[i]] = variants[i];   // ... unless the table has them apart
     });
 }
 

@@ -1767,7 +1767,7 @@ static void launch_by_id(Context &c, int id, const StencilArgs<ST> &a, const GT 
 template <typename ST, typename GT, int EPI>
 static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int nf, int prec)
 {
-    const int key = (prec * 8 + EPI) * 64 + (nf < 63 ? nf : 63);
+    const int key = tuning_key(prec, EPI == EPI_K && a.canon ? TUNE_K_CANON : EPI, nf);
     auto it = c.tuned.find(key);
     if (it != c.tuned.end()) return it->second;
     if (c.no_alloc) return 1;   // timing would need workspace and events: fixed shape, not recorded
@@ -1782,8 +1782,14 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     // are timed one by one, by events attached to the dispatches.
     StencilArgs<ST> t = a;
     t.stop = nullptr;
-    t.canon = nullptr;   // the packed store, whatever the call wants: one choice per key
-    t.out = (ST *)c.buf("tune_out", field_bytes(c.g, prec) * nf);
+    // with the store of the call: the canonical one, 192-byte rows of a site
+    // whatever the precision, costs as much as the rest of an FP16 launch, and
+    // another variant hides it best (H and K on twelve FP16 fields of 24^3 x 48:
+    // 963 us with the variant chosen under the packed store, 763 with the one
+    // chosen under its own; FP32, one field: 118 and 96 us)
+    void *scratch = c.buf("tune_out", field_bytes(c.g, a.canon ? OVL_F64 : prec) * nf);
+    t.canon = a.canon ? (double2 *)scratch : nullptr;
+    t.out = (ST *)scratch;
     t.partial = (double *)c.buf("tune_part", sizeof(double) * 3 * (size_t)nf * stencil_tiles_max(c.g));
     constexpr int REPS = 5;
     struct Events {
@@ -1903,14 +1909,14 @@ int stencil_k2_dot(Context &c, int prec, const void *t, void *w, int nf, double 
                    const void *r, double *partial, const int *stop, int it, const int *itb)
 {
     stencil(c, EPI_K2DOT, prec, t, w, nf, rho, s0, p, partial, stop, it, r, itb);
-    const int key = (prec * 8 + EPI_K2DOT) * 64 + (nf < 63 ? nf : 63);
+    const int key = tuning_key(prec, EPI_K2DOT, nf);
     const int v = c.tuned.count(key) ? c.tuned[key] : 1;
     return (int)stencil_tiles(c.g, v);
 }
 
 int stencil_variant(Context &c, int epi, int prec, int nf)
 {
-    const int key = (prec * 8 + epi) * 64 + (nf < 63 ? nf : 63);
+    const int key = tuning_key(prec, epi, nf);
     const auto it = c.tuned.find(key);
     return it == c.tuned.end() ? -1 : it->second;
 }

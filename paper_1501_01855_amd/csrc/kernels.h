@@ -11,6 +11,11 @@ enum Epilogue {
     EPI_KPLUS = 3   // out = K in + aux
 };
 
+// Key of a launch shape's choice of variant: by epilogue, and K stored in the
+// canonical layout by a number of its own (H is always stored there).
+constexpr int TUNE_K_CANON = 4;
+inline int tuning_key(int prec, int epi, int nf) { return (prec * 8 + epi) * 64 + (nf < 63 ? nf : 63); }
+
 template <typename ST>
 struct StencilArgs {
     Geom g;
