@@ -1092,28 +1092,34 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
 }
 
 // Right-hand sides of one multi-shift CG.  An iteration goes through five fields
-// per right-hand side (p, t, w and the residuals of two iterations) and the
-// links; while they stay within about the 256 MB of the Infinity Cache they come
-// from there.  More right-hand sides are solved in as few equal batches as fit,
-// if at least two fit at a time.  Measured, twelve right-hand sides together and
-// in batches: FP32 16^3 x 32 40.4 and 35.6 ms, 20^4 52.0 and 47.8 ms, 14^3 x 28
-// 23.1 and 22.3 ms; FP64 12^3 x 24 48.6 and 46.6 ms.  A smaller limit splits six
-// fields of the last two that just fit, which takes 10 % longer.  In FP16 the
-// stencils are bound by their instructions and batches gain nothing.
+// per right-hand side it works on (p, t, w and the residuals of two iterations)
+// and the links; while they about fit the Infinity Cache (268e6 bytes) they come
+// from there.  More of them are solved in as few equal batches as fit, if at
+// least two fit at a time.  Fields that are skipped (eta <= 0: converged, or of
+// another precision) cost no traffic and don't count.  Measured, twelve
+// right-hand sides together and in batches: FP32 16^3 x 32 40.4 and 35.6 ms,
+// 20^4 52.0 and 47.8 ms, 14^3 x 28 23.1 and 22.3 ms; FP64 12^3 x 24 48.6 and
+// 46.6 ms.  The limit is the measured one and lies a little above the cache's
+// size: batches of 277e6 bytes (four fields of 16^3 x 32) and six fields of the
+// last two lattices are faster whole, the latter by 10 %, as part of the data
+// still comes from the cache.  In FP16 the stencils are bound by their
+// instructions and batches gain nothing.
 static constexpr double CACHE_BYTES = 280e6;
-static int fields_per_call(const Context &c, int prec, int nf)
+static int fields_per_call(const Context &c, int prec, int nf, const double *eta)
 {
+    int active = 0;
+    for (int f = 0; f < nf; ++f) active += eta[f] > 0.0;
     const double S = (double)field_bytes(c.g, prec), room = CACHE_BYTES - stencil_link_bytes(c.g, prec);
     const int fit = room > 0.0 ? (int)std::min(room / (5.0 * S), 1e6) : 0;
-    if (prec == OVL_HALF || fit < 2 || fit >= nf) return nf;
-    const int calls = (nf + fit - 1) / fit;
+    if (prec == OVL_HALF || fit < 2 || fit >= active) return nf;
+    const int calls = (active + fit - 1) / fit;
     return (nf + calls - 1) / calls;
 }
 
 void sign_mscg(Context &c, double rho, const ovl_zolo &z, const void *in, void *out, int nf,
                const double *eta, int prec, int maxiter, ovl_stats *st)
 {
-    const int per = fields_per_call(c, prec, nf);
+    const int per = fields_per_call(c, prec, nf, eta);
     const size_t FB = field_bytes(c.g, prec);
     std::vector<int64_t> iters;
     int64_t total = 0;
@@ -1121,6 +1127,11 @@ void sign_mscg(Context &c, double rho, const ovl_zolo &z, const void *in, void *
         const int n = std::min(per, nf - f);
         const void *i = (const char *)in + FB * f;
         void *o = (char *)out + FB * f;
+        if (per < nf && std::none_of(eta + f, eta + f + n, [](double e) { return e > 0.0; })) {
+            zero_fields(c, o, n, prec);
+            iters.insert(iters.end(), n, 0);
+            continue;
+        }
         if (prec == OVL_F64)
             sign_t<double2>(c, rho, z, i, o, n, eta + f, prec, maxiter, st);
         else if (prec == OVL_F32)
