@@ -968,10 +968,12 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
     const int CHUNK = replay ? std::max(4, group) : 4;
     const size_t pst = (size_t)(FB / sizeof(ST)) * nf;   // elements between ring slots
     int *itb = (int *)c.buf("ms_itb", sizeof(int));
-    auto run_flush = [&](int j0, const int *ib) {   // the group that starts at iteration *ib + j0
+    // the group that starts at iteration *ib + j0; the source is read in the first
+    // group only, which is never replayed, so a graph does not depend on it
+    auto run_flush = [&](int j0, const int *ib) {
         PendingEvent pe;
         if (c.prof) c.prof_begin(pe, KERN_SHIFT, prec, 0.0);
-        launch_k(c, c.prof ? &pe : nullptr, flush, dim3(nflush, nf), dim3(flush_nt), 0, src, ring, y, p,
+        launch_k(c, c.prof ? &pe : nullptr, flush, dim3(nflush, nf), dim3(flush_nt), 0, ib ? pb : src, ring, y, p,
                  MscgFlush{S, coef, group, kdev, stop, ib, j0}, V);
         if (c.prof) c.prof_end(pe);
         OVL_HIP(hipGetLastError());
@@ -1000,7 +1002,7 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
             for (int j = 0; j < CHUNK; ++j) one_iter(it + j, nullptr);
         } else {
             if (!gexec) gexec = chunk_graph(c, prec, nf, all, CHUNK, itb, [&](int j) { one_iter(j, itb); },
-                                            {src, ring, t, w, y, p, pb, S, kdev, coef, stop, part, rr_part, hpd,
+                                            {ring, t, w, y, p, pb, S, kdev, coef, stop, part, rr_part, hpd,
                                              (const void *)(intptr_t)group, (const void *)(intptr_t)nstep},
                                             {rho, k.s0});
             if (it == CHUNK) {
