@@ -254,6 +254,7 @@ static void link_force_t(Context &c, double rho, double mu, const ovl_zolo &z, S
         k_psi_gradient<ST><<<dim3((unsigned)((n + 255) / 256), nf), 256, 0, c.stream>>>(
             xb, lstride, w, nz, chip64, dpsi, 0.5 * (1.0 + mu), 0.5 * (1.0 - mu), g.V);
         OVL_HIP(hipGetLastError());
+        if (st) st->sign_calls[prec] += nf;   // eps(K) chi' of every field
     }
     ForceCoef k{};
     for (int l = 0; l < nz; ++l) k.w[l] = -0.25 * (1.0 - mu) * z.omega[l];
