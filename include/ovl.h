@@ -385,7 +385,7 @@ ovl_status ovl_profile_read(ovl_context *ctx, int32_t kernel, int32_t prec, int6
 ovl_status ovl_stream_bench(ovl_context *ctx, int32_t kind, const void *src_dev, void *dst_dev, int64_t bytes,
                             int32_t reps, double *ms_host);
 
-/* Execution options of a context (value 0 = off, 1 = on):
+/* Execution options of a context (value 0 = off, 1 = on, but for the last):
  *   OVL_OPT_GRAPHS   (default off) the multi-shift CG replays a graph of four
  *                    iterations per chunk after the first chunk (off: every
  *                    kernel is launched on its own); results are identical.
@@ -422,9 +422,18 @@ ovl_status ovl_stream_bench(ovl_context *ctx, int32_t kind, const void *src_dev,
  *                    ||D u - c|| < eps ||b|| ||u|| / ||r||: the sign function
  *                    to 2 eps ||b|| / ((1 - mu) ||r||), looser as the outer
  *                    residual r falls; off: ||D u - c|| <= eps ||b|| / 4 at
- *                    every outer step. */
+ *                    every outer step.
+ *   OVL_OPT_WORKSPACE_KIB (default 0: no limit; the value is a number of KiB)
+ *                    the device memory the context holds (ovl_device_bytes)
+ *                    may not grow beyond this: a call that needs more returns
+ *                    OVL_ERR_NOMEM.  Near the limit, as when the device itself
+ *                    is nearly full, calls go without the buffers that only make
+ *                    them faster, and give back what earlier calls left; the
+ *                    order of sums over iterations, and in FP16 the rounding of
+ *                    the shift vectors, then differ from those of a call with
+ *                    memory to spare. */
 enum { OVL_OPT_GRAPHS = 1, OVL_OPT_AUTOTUNE = 2, OVL_OPT_ADAPTIVE_NZ = 3, OVL_OPT_BOUND_PRINTED = 4,
-       OVL_OPT_TWO_ROW_LINKS = 5, OVL_OPT_OUTER_PRINTED = 6 };
+       OVL_OPT_TWO_ROW_LINKS = 5, OVL_OPT_OUTER_PRINTED = 6, OVL_OPT_WORKSPACE_KIB = 7 };
 ovl_status ovl_set_option(ovl_context *ctx, int32_t option, int32_t value);
 
 /* The loaded links (Sec. 1, eq. 2: U_mu(x) in SU(3)).  *su3_deviation

@@ -21,6 +21,7 @@ MAX_NZ = 64
 KERN_STENCIL, KERN_SHIFT = 0, 1
 N_STENCIL_VARIANTS = 23   # launch variants of the stencil (tuning-table values 0 .. 22)
 OPT_GRAPHS, OPT_AUTOTUNE, OPT_ADAPTIVE_NZ, OPT_BOUND_PRINTED, OPT_TWO_ROW_LINKS, OPT_OUTER_PRINTED = 1, 2, 3, 4, 5, 6
+OPT_WORKSPACE_KIB = 7
 
 STATUS = {0: "OK", -1: "ERR_ARG", -2: "ERR_HIP", -3: "ERR_NOMEM", -4: "ERR_NOT_CONVERGED",
           -5: "ERR_BREAKDOWN", -6: "ERR_UNSUPPORTED", -7: "ERR_STATE"}
@@ -409,7 +410,8 @@ class Context:
         return ms.value
 
     def set_option(self, option, value):
-        _check(lib().ovl_set_option(self._h, int(option), int(bool(value))))
+        _check(lib().ovl_set_option(self._h, int(option),
+                                    int(value) if option == OPT_WORKSPACE_KIB else int(bool(value))))
 
     def gauge_info(self):
         """(largest deviation of the links' third rows from the two-row rebuild,

@@ -227,15 +227,18 @@ static void link_force_t(Context &c, double rho, double mu, const ovl_zolo &z, S
     // Both sources in one multi-shift CG (one launch carries both, links read
     // once), its shift vectors [l][2 nf], while the device has room for twice
     // as many; else one after the other, [l][nf] each.
-    bool together = true;
-    if (c.pool["ms_p"].bytes < 2 * half_bytes) {
-        size_t avail = 0, total = 0;
-        OVL_HIP(hipMemGetInfo(&avail, &total));
-        together = 2 * half_bytes + 16 * FB * nf <= avail / 2;
-    }
+    // (22 more fields per right-hand side: those of the CG and its ring)
+    const size_t want = 2 * half_bytes + 22 * FB * nf, have = c.idle_bytes();
+    bool together = want <= have || want <= have + c.room() / 2;
     if (together) {
-        shifts_mscg(c, rho, z, src, x, 2 * nf, e.data(), prec, maxiter, st);
-    } else {
+        try {
+            shifts_mscg(c, rho, z, src, x, 2 * nf, e.data(), prec, maxiter, st);
+        } catch (const Error &err) {
+            if (err.code != OVL_ERR_NOMEM) throw;
+            together = false;
+        }
+    }
+    if (!together) {
         shifts_mscg(c, rho, z, src, x, nf, e.data(), prec, maxiter, st);
         shifts_mscg(c, rho, z, src + nf * fs, x + (int64_t)nf * nz * fs, nf, e.data() + nf, prec, maxiter, st);
     }

@@ -270,7 +270,7 @@ ovl_status ovl_lowmodes_set(ovl_context *ctx, int32_t n, const double *evals_hos
         ctx->low_evals.clear();
         if (n == 0) return;
         const size_t FB = field_bytes(ctx->g, OVL_F64);
-        OVL_HIP(hipMalloc(&ctx->low, FB * n));
+        OVL_HIP(ctx->device_alloc((void **)&ctx->low, FB * n));
         ctx->bytes_held += (int64_t)FB * n;
         pack_spinor(*ctx, evecs_dev, ctx->low, n, OVL_F64);
         ctx->low_evals.assign(evals_host, evals_host + n);
@@ -726,6 +726,11 @@ ovl_status ovl_set_option(ovl_context *ctx, int32_t option, int32_t value)
 {
     return guard([&] {
         check_ctx(ctx);
+        if (option == OVL_OPT_WORKSPACE_KIB) {
+            OVL_REQUIRE(value >= 0, OVL_ERR_ARG, "the workspace limit must not be negative");
+            ctx->ws_limit = (size_t)value * 1024;
+            return;
+        }
         OVL_REQUIRE(value == 0 || value == 1, OVL_ERR_ARG, "option value must be 0 or 1");
         if (option == OVL_OPT_GRAPHS)
             ctx->use_graphs = value != 0;

@@ -86,6 +86,9 @@ struct Geom {
     int32_t two_row64;   // FP64 stencils read two rows and the third's difference from its rebuild (the links exactly)
 };
 
+// Device bytes of the FP64 two-row links.
+inline int64_t two_row64_bytes(const Geom &g) { return g.Pu * 4 * (6 * 16 + 3 * 8); }
+
 inline Geom make_geom(const int32_t d[4])
 {
     Geom g;
@@ -138,6 +141,7 @@ inline Geom make_geom(const int32_t d[4])
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
+    bool idle = false;   // holds nothing that is still needed: may be given back when memory is short
 };
 
 // Half-precision spinor storage: 12 complex FP16 values per site in three

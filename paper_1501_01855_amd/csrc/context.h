@@ -1,6 +1,8 @@
 // The library context: one lattice geometry, its gauge field in every
 // precision, the kernel low modes, workspace and profiling state.
 #pragma once
+#include <functional>
+#include <initializer_list>
 #include <map>
 #include <tuple>
 #include <utility>
@@ -85,9 +87,14 @@ struct Context {
     hipEvent_t ms_ev[2] = {nullptr, nullptr};
     std::vector<char> ms_const_last;
 
-    // named workspace; grows on demand, freed at destroy
+    // Named workspace; grows on demand, freed at destroy.  What a call can do
+    // without (rings of residuals and of basis vectors, the second half of the
+    // adjoint's shift vectors, the FP64 two-row links) is taken only while memory
+    // is plentiful and given back by reclaim() when an allocation fails.
     std::map<std::string, DevBuf> pool;
     int64_t bytes_held = 0;
+    size_t ws_limit = 0;              // OVL_OPT_WORKSPACE_KIB, in bytes (0: none)
+    std::function<void()> shrink;     // set while a solver holds basis vectors it can do without
 
     // host staging (pinned)
     void *pinned = nullptr;
@@ -127,7 +134,15 @@ struct Context {
     GraphRec *rec = nullptr;
     std::map<std::string, hipGraphExec_t> graphs;
 
-    void *buf(const std::string &name, size_t bytes);
+    void *buf(const std::string &name, size_t bytes);       // OVL_ERR_NOMEM if nothing helps
+    void *opt_buf(const std::string &name, size_t bytes);   // null if it is not to be had as things are
+    void release(const std::string &name);
+    void idle(std::initializer_list<const char *> names);   // their contents are needed no more
+    size_t idle_bytes() const;
+    size_t room() const;   // bytes the context may still allocate
+    // hipMalloc, giving back what the context can do without if that is needed
+    hipError_t device_alloc(void **p, size_t bytes);
+    bool reclaim(int level);
     void *host_stage(size_t bytes);
     // small results that kernels write straight into host memory (pinned,
     // mapped, coherent): host address, and the device address of the same

@@ -15,26 +15,103 @@ static thread_local std::string g_last_error;
 void set_error(const std::string &msg) { g_last_error = msg; }
 const char *last_error() { return g_last_error.c_str(); }
 
+size_t Context::room() const
+{
+    size_t avail = 0, total = 0;
+    OVL_HIP(hipMemGetInfo(&avail, &total));
+    if (ws_limit) avail = std::min(avail, ws_limit > (size_t)bytes_held ? ws_limit - (size_t)bytes_held : 0);
+    return avail;
+}
+
+// Gives back memory the context can do without: buffers that hold nothing any
+// more (level 0), a running solver's spare basis vectors (1), the FP64 two-row
+// links (2: the full links are always there and give the same values).
+bool Context::reclaim(int level)
+{
+    const int64_t before = bytes_held;
+    if (level == 0) {
+        for (auto &kv : pool)
+            if (kv.second.idle) release(kv.first);
+    } else if (level == 1) {
+        if (shrink) shrink();
+    } else if (U64r) {
+        OVL_HIP(hipStreamSynchronize(stream));
+        OVL_HIP(hipFree(U64r));
+        U64r = nullptr;
+        bytes_held -= two_row64_bytes(g);
+        update_link_form(*this);
+    }
+    return bytes_held < before;
+}
+
+hipError_t Context::device_alloc(void **p, size_t bytes)
+{
+    hipError_t e = hipErrorOutOfMemory;
+    for (int level = -1; level < 3; ++level) {
+        if (level >= 0 && !reclaim(level)) continue;
+        if (ws_limit && (size_t)bytes_held + bytes > ws_limit) continue;
+        e = hipMalloc(p, bytes);
+        if (e == hipSuccess) return e;
+        (void)hipGetLastError();   // reported by the caller, not by the next launch
+    }
+    *p = nullptr;
+    return e;
+}
+
+void Context::release(const std::string &name)
+{
+    DevBuf &b = pool[name];
+    if (b.p) {
+        OVL_HIP(hipStreamSynchronize(stream));
+        OVL_HIP(hipFree(b.p));
+        bytes_held -= (int64_t)b.bytes;
+    }
+    b = DevBuf{};
+}
+
+void Context::idle(std::initializer_list<const char *> names)
+{
+    for (const char *n : names) pool[n].idle = true;
+}
+
+size_t Context::idle_bytes() const
+{
+    size_t s = 0;
+    for (const auto &kv : pool)
+        if (kv.second.idle) s += kv.second.bytes;
+    return s;
+}
+
 void *Context::buf(const std::string &name, size_t bytes)
 {
     DevBuf &b = pool[name];
+    b.idle = false;
     if (b.bytes < bytes) {
-        if (b.p) {
-            OVL_HIP(hipStreamSynchronize(stream));
-            OVL_HIP(hipFree(b.p));
-            bytes_held -= (int64_t)b.bytes;
-            b.p = nullptr;
-            b.bytes = 0;
-        }
-        hipError_t e = hipMalloc(&b.p, bytes);
-        if (e != hipSuccess) {
-            b.p = nullptr;
+        release(name);
+        if (device_alloc(&b.p, bytes) != hipSuccess)
             throw Error{OVL_ERR_NOMEM, "workspace '" + name + "': hipMalloc of " + std::to_string(bytes) +
                                            " bytes failed"};
+        b.bytes = bytes;
+        bytes_held += (int64_t)bytes;
+    }
+    return b.p;
+}
+
+void *Context::opt_buf(const std::string &name, size_t bytes)
+{
+    DevBuf &b = pool[name];
+    if (b.bytes < bytes) {
+        release(name);
+        if (ws_limit && (size_t)bytes_held + bytes > ws_limit) return nullptr;
+        if (hipMalloc(&b.p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            b.p = nullptr;
+            return nullptr;
         }
         b.bytes = bytes;
         bytes_held += (int64_t)bytes;
     }
+    b.idle = false;
     return b.p;
 }
 
@@ -107,7 +184,7 @@ const void *Context::low_basis(int prec)
     if (prec == OVL_F64 || n_low == 0) return low;
     if (!low_lp[prec]) {
         const size_t B = field_bytes(g, prec) * n_low;
-        OVL_HIP(hipMalloc(&low_lp[prec], B));
+        OVL_HIP(device_alloc(&low_lp[prec], B));
         bytes_held += (int64_t)B;
         convert_spinor(*this, low, OVL_F64, low_lp[prec], prec, n_low);
     }

@@ -98,7 +98,7 @@ __global__ void k_pack_gauge(const double2 *__restrict__ canon, double2 *__restr
     if (s >= V) return;
     // FP64 two-row form (the planes ld_link reads for d2r12); where a difference
     // does not fit (k_su3_dev tells) the full form is used
-    for (int mu = 0; mu < 4; ++mu) {
+    for (int mu = 0; mu < 4 && U64r != nullptr; ++mu) {
         cplx<double> u[9];
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
@@ -289,14 +289,24 @@ static constexpr double TWO_ROW_TOL64 = 0x1p-43;
 void pack_gauge(Context &c, const double *canon)
 {
     const Geom &g = c.g;
-    if (!c.U64) {
-        OVL_HIP(hipMalloc(&c.U64, (size_t)g.Pu * 36 * sizeof(double2)));
-        OVL_HIP(hipMalloc(&c.U64r, (size_t)g.Pu * 4 * (6 * sizeof(double2) + 3 * sizeof(int2))));
-        OVL_HIP(hipMalloc(&c.U32, (size_t)g.Pu * 36 * sizeof(float2)));
-        OVL_HIP(hipMalloc(&c.U16, (size_t)g.Pu * 36 * sizeof(__half2)));
-        OVL_HIP(hipMalloc(&c.U32r, (size_t)g.Pu * 24 * sizeof(float2)));
-        OVL_HIP(hipMalloc(&c.U16r, (size_t)g.Pu * 24 * sizeof(__half2)));
-        c.bytes_held += (int64_t)g.Pu * (36 * (16 + 8 + 4) + 24 * (8 + 4) + 4 * (6 * 16 + 3 * 8));
+    auto need = [&](auto *&p, size_t bytes_per_site) {   // also after a load that ran out of memory half-way
+        const size_t bytes = (size_t)g.Pu * bytes_per_site;
+        if (p) return;
+        OVL_HIP(c.device_alloc((void **)&p, bytes));
+        c.bytes_held += (int64_t)bytes;
+    };
+    need(c.U64, 36 * sizeof(double2));
+    need(c.U32, 36 * sizeof(float2));
+    need(c.U16, 36 * sizeof(__half2));
+    need(c.U32r, 24 * sizeof(float2));
+    need(c.U16r, 24 * sizeof(__half2));
+    if (!c.U64r && (size_t)two_row64_bytes(g) <= c.room() / 4) {   // the full FP64 links do without it
+        if (hipMalloc(&c.U64r, (size_t)two_row64_bytes(g)) == hipSuccess) {
+            c.bytes_held += two_row64_bytes(g);
+        } else {
+            (void)hipGetLastError();
+            c.U64r = nullptr;
+        }
     }
     k_pack_gauge<<<site_blocks(g), 256, 0, c.stream>>>((const double2 *)canon, c.U64, c.U32, (__half2 *)c.U16,
                                                        (float2 *)c.U32r, (__half2 *)c.U16r, (double2 *)c.U64r, g.V, g.Pu);
@@ -323,7 +333,7 @@ void pack_gauge(Context &c, const double *canon)
 void update_link_form(Context &c)
 {
     c.g.two_row = (c.two_row_opt && c.have_gauge && c.su3_dev >= 0.0 && c.su3_dev <= TWO_ROW_TOL) ? 1 : 0;
-    c.g.two_row64 = c.g.two_row && c.third_fits && c.su3_dev <= TWO_ROW_TOL64 ? 1 : 0;
+    c.g.two_row64 = c.g.two_row && c.U64r && c.third_fits && c.su3_dev <= TWO_ROW_TOL64 ? 1 : 0;
 }
 
 // ------------------------------------------------------------- stencil kernel
@@ -1764,6 +1774,13 @@ static void launch_by_id(Context &c, int id, const StencilArgs<ST> &a, const GT 
     }
 }
 
+// The scratch output of timed launches.
+static void reserve_tuning(Context &c, int prec, int nf)
+{
+    c.buf("tune_out", field_bytes(c.g, prec) * nf);
+    c.buf("tune_part", sizeof(double) * 3 * (size_t)nf * stencil_tiles_max(c.g));
+}
+
 template <typename ST, typename GT, int EPI>
 static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int nf, int prec)
 {
@@ -1787,10 +1804,10 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     // another variant hides it best (H and K on twelve FP16 fields of 24^3 x 48:
     // 963 us with the variant chosen under the packed store, 763 with the one
     // chosen under its own; FP32, one field: 118 and 96 us)
-    void *scratch = c.buf("tune_out", field_bytes(c.g, a.canon ? OVL_F64 : prec) * nf);
-    t.canon = a.canon ? (double2 *)scratch : nullptr;
-    t.out = (ST *)scratch;
-    t.partial = (double *)c.buf("tune_part", sizeof(double) * 3 * (size_t)nf * stencil_tiles_max(c.g));
+    reserve_tuning(c, a.canon ? OVL_F64 : prec, nf);   // held since before the links were chosen
+    t.canon = a.canon ? (double2 *)c.pool["tune_out"].p : nullptr;
+    t.out = (ST *)c.pool["tune_out"].p;
+    t.partial = (double *)c.pool["tune_part"].p;
     constexpr int REPS = 5;
     struct Events {
         hipEvent_t e[2 * REPS] = {};
@@ -1841,6 +1858,7 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     for (int v : ids)
         if (ms_best[v] < ms_best[best]) best = v;
     OVL_HIP(hipGetLastError());
+    c.idle({"tune_out", "tune_part"});
     return c.tuned[key] = best;
 }
 
@@ -1880,6 +1898,10 @@ void stencil(Context &c, int epi, int prec, const void *in, void *out, int nf, d
              const int *itb, double2 *canon)
 {
     OVL_REQUIRE(c.have_gauge, OVL_ERR_STATE, "no gauge field loaded");
+    // room for timing this launch before the links are chosen: an allocation may
+    // cost the FP64 two-row links
+    if (c.autotune && !c.no_alloc && !c.tuned.count(tuning_key(prec, epi == EPI_K && canon ? TUNE_K_CANON : epi, nf)))
+        reserve_tuning(c, canon ? OVL_F64 : prec, nf);
     if (prec == OVL_F64) {
         StencilArgs<double2> a{c.g, (const double2 *)in, (double2 *)out, (const double2 *)aux,
                                (const double2 *)aux2, 4.0 - rho, sigma, partial, stop, it, itb, canon};

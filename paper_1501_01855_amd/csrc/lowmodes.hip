@@ -162,7 +162,7 @@ void lowmodes_compute(Context &c, double rho, int n_low, double tol, double *eva
         c.bytes_held -= (int64_t)FB * c.n_low;
         c.low = nullptr;
     }
-    OVL_HIP(hipMalloc(&c.low, FB * n_low));
+    OVL_HIP(c.device_alloc((void **)&c.low, FB * n_low));
     c.bytes_held += (int64_t)FB * n_low;
     copy_fields(c, Y, c.low, n_low, OVL_F64);
     c.n_low = n_low;

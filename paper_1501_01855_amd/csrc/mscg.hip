@@ -780,6 +780,7 @@ static hipGraphExec_t chunk_graph(Context &c, int prec, int nf, bool all, int ch
     const int head[7] = {prec, nf, all ? 1 : 0, chunk, stencil_variant(c, EPI_K, prec, nf),
                          stencil_variant(c, EPI_K2DOT, prec, nf), c.g.two_row + 2 * c.g.two_row64};
     put(head, sizeof(head));
+    put(&c.U64r, sizeof(c.U64r));
     for (const void *q : ptrs) put(&q, sizeof(q));
     for (double v : vals) put(&v, sizeof(v));
     put(&itb, sizeof(itb));
@@ -827,17 +828,26 @@ static unsigned resident_blocks(Context &c, int &per_cu, K *kernel, int nt)
     return (unsigned)(per_cu * c.num_cu);
 }
 
-// The ring of residuals: GROUP slots (iterations per group), halved while the ring would take more than a quarter of the
-// free device memory (one slot is the residual updated in place).
+// The ring of residuals: GROUP slots (iterations per group), halved while the
+// ring would take more than a quarter of the memory to be had (one slot is the
+// residual updated in place).
 static void *residual_ring(Context &c, size_t field_set, int &group)
 {
-    if (c.pool["ms_ring"].bytes < field_set * group) {
-        size_t avail = 0, total = 0;
-        OVL_HIP(hipMemGetInfo(&avail, &total));
-        while (group > 1 && field_set * group > avail / 4) group /= 2;
+    const size_t held = c.pool["ms_ring"].bytes;
+    if (held < field_set * group) {
+        const size_t room = c.room() + held;
+        while (group > 1 && field_set * group > room / 4) group /= 2;
     }
-    return c.buf("ms_ring", field_set * group);
+    for (; group > 1; group /= 2)
+        if (void *p = c.opt_buf("ms_ring", field_set * group)) return p;
+    return c.buf("ms_ring", field_set);
 }
+
+// The buffers of a multi-shift CG hold nothing once it has ended.
+struct MscgScratch {
+    Context &c;
+    ~MscgScratch() { c.idle({"ms_src", "ms_pb", "ms_t", "ms_w", "ms_y", "ms_p", "ms_ring"}); }
+};
 
 template <typename ST>
 static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, void *out, int nf,
@@ -886,6 +896,7 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
         OVL_REQUIRE(z.sigma[l] > 0.0 && z.omega[l] > 0.0, OVL_ERR_ARG, "Zolotarev coefficients must be positive");
 
     const bool low = c.n_low > 0 && !all;
+    const MscgScratch scratch{c};
     // the source: the input itself, or its part off the low modes (whose exact
     // part then waits in the output until the final K)
     const ST *src = low ? (const ST *)c.buf("ms_src", FB * nf) : (const ST *)in;

@@ -295,6 +295,14 @@ struct SumrRec {   // one iteration's coefficients of one field
     double ar, ai, kr, ki, lr, li, er, ei;
     int act, pad;
 };
+__device__ __forceinline__ SumrRec sumr_rec(const SumrCoef &k, int f)
+{
+    return SumrRec{k.ar[f], k.ai[f], k.kr[f], k.ki[f], k.lr[f], k.li[f], k.er[f], k.ei[f], k.act[f], 0};
+}
+__global__ void k_sumr_rec(SumrCoef k, SumrRec *rec, int nf)
+{
+    if ((int)threadIdx.x < nf) rec[threadIdx.x] = sumr_rec(k, threadIdx.x);
+}
 
 // u = gamma_5 s: s in the storage ST of the sign call (one lane per site), or u
 // itself (ST = double2, element by element); and ||q_new||^2 per block.
@@ -306,7 +314,7 @@ __global__ __launch_bounds__(256) void k_sumr_basis(SumrCoef k, SumrRec *rec, do
     const int f = blockIdx.y;
     double nn = 0.0;
     if (blockIdx.x == 0 && threadIdx.x == 0)
-        rec[f] = SumrRec{k.ar[f], k.ai[f], k.kr[f], k.ki[f], k.lr[f], k.li[f], k.er[f], k.ei[f], k.act[f], 0};
+        rec[f] = sumr_rec(k, f);
     if (k.act[f]) {
         const cplx<double> gam{k.gr[f], k.gi[f]};
         const double sg = k.sigma[f], is = 1.0 / sg;
@@ -343,10 +351,12 @@ __global__ __launch_bounds__(256) void k_sumr_basis(SumrCoef k, SumrRec *rec, do
 }
 
 // The group's iterations j = 0 .. cnt - 1 (coefficients rec[j][f]) on omega, p
-// and x; iteration j has q_old in ring slot first - 1 + j and q in first + j
-// (modulo slots, n elements per field, nf fields per slot).
-__global__ __launch_bounds__(256) void k_sumr_solution(const SumrRec *__restrict__ rec, int cnt,
-                                                       const double2 *__restrict__ ring, int first, int slots,
+// and x; iteration j has q_old in basis.q[j] and q in basis.q[j + 1] (n elements
+// per field).
+struct SumrBasis {
+    const double2 *q[SUMR_GROUP + 1];
+};
+__global__ __launch_bounds__(256) void k_sumr_solution(const SumrRec *__restrict__ rec, int cnt, SumrBasis basis,
                                                        double2 *__restrict__ om, double2 *__restrict__ p,
                                                        double2 *__restrict__ x, int64_t n)
 {
@@ -354,12 +364,12 @@ __global__ __launch_bounds__(256) void k_sumr_solution(const SumrRec *__restrict
     bool any = false;
     for (int j = 0; j < cnt; ++j) any = any || rec[j * nf + f].act != 0;
     if (!any) return;
-    const int64_t o = (int64_t)f * n, ss = (int64_t)nf * n;
+    const int64_t o = (int64_t)f * n;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         double2 qv[SUMR_GROUP + 1];
 #pragma unroll
         for (int j = 0; j <= SUMR_GROUP; ++j)
-            if (j <= cnt) qv[j] = ring[((first - 1 + j + slots) % slots) * ss + o + i];
+            if (j <= cnt) qv[j] = basis.q[j][o + i];
         const double2 ov = om[o + i], pv = p[o + i], xv = x[o + i];
         cplx<double> O{ov.x, ov.y}, P{pv.x, pv.y}, X{xv.x, xv.y};
 #pragma unroll
@@ -413,6 +423,41 @@ struct SumrField {
     bool active = false, need_init = true;
 };
 
+// SUMR's basis vectors, the last ones of nf fields each: slots round a ring,
+// which ends with the solve.
+class SumrRing {
+    Context &c;
+    std::vector<double2 *> q;
+    std::vector<std::string> names;
+
+public:
+    explicit SumrRing(Context &cc) : c(cc) {}
+    ~SumrRing()
+    {
+        c.shrink = nullptr;
+        for (const auto &s : names) c.pool[s].idle = true;
+    }
+    static std::string name(int i) { return "s_q" + std::to_string(i); }
+    void add(void *p, const std::string &s)
+    {
+        q.push_back((double2 *)p);
+        names.push_back(s);
+    }
+    int size() const { return (int)q.size(); }
+    double2 *slot(int i) const { return q[(i + size()) % size()]; }
+    // only slots a and b stay, as 0 and 1
+    void keep(int a, int b)
+    {
+        const int n = size();
+        a = (a + n) % n;
+        b = (b + n) % n;
+        for (int i = 0; i < n; ++i)
+            if (i != a && i != b) c.release(names[i]);
+        q = {q[a], q[b]};
+        names = {names[a], names[b]};
+    }
+};
+
 // relSUMR for (1 + rho U) x_f = bp_f on the fields with mask[f], x holding x0
 // (zero when x_zero).  Ax0 (nullable) holds (1 + rho U) x0 when the caller
 // knows it (the deflated start supplies it from the stored D psi', Sec. 4),
@@ -431,28 +476,37 @@ static void sumr(Context &c, const ovl_zolo &z, const ovl_solver_params &prm, do
     double2 *u = (double2 *)c.buf("s_u", FB * nf);
     const int64_t n = 12 * c.g.V;
     const int nblk = 512;
-    // the ring of q's: a group's, the one before it and the one after; smaller
-    // groups where device memory is short
-    int group = SUMR_GROUP;
-    if (c.pool["s_q"].bytes < FB * nf * (group + 2)) {
-        size_t avail = 0, total = 0;
-        OVL_HIP(hipMemGetInfo(&avail, &total));
-        while (group > 1 && FB * nf * (group + 2) > avail / 4) group /= 2;
-    }
-    const int slots = group + 2;
-    double2 *ring = (double2 *)c.buf("s_q", FB * nf * slots);
     SumrRec *rec = (SumrRec *)c.buf("s_rec", sizeof(SumrRec) * SUMR_GROUP * nf);
-    auto slot = [&](int i) { return ring + (size_t)((i + slots) % slots) * n * nf; };
+    double *part = (double *)c.buf("s_part", sizeof(double) * nblk * nf);
+    // the ring of q's: q_old and q, and, where memory allows, a group of up to
+    // SUMR_GROUP iterations' more (spare ones are given back when it runs short)
+    SumrRing ring{c};
+    for (int i = 0; i < 2; ++i) ring.add(c.buf(SumrRing::name(i), FB * nf), SumrRing::name(i));
+    for (int want = SUMR_GROUP + 2; want > 2 && ring.size() == 2; want = want / 2 + 1) {
+        size_t missing = 0;
+        for (int i = 2; i < want; ++i) missing += c.pool[SumrRing::name(i)].bytes < FB * nf ? FB * nf : 0;
+        if (missing > 0 && missing > c.room() / 4) continue;
+        for (int i = 2; i < want; ++i) {
+            void *s = c.opt_buf(SumrRing::name(i), FB * nf);
+            if (!s) break;   // keep what there is
+            ring.add(s, SumrRing::name(i));
+        }
+    }
     int cur = 1, waiting = 0;   // slot of q, iterations whose omega, p, x are due
-    double2 *q = slot(cur), *qold = slot(cur - 1);
+    double2 *q = ring.slot(cur), *qold = ring.slot(cur - 1);
     auto settle = [&] {
         if (waiting == 0) return;
-        k_sumr_solution<<<dim3(1024, nf), 256, 0, c.stream>>>(rec, waiting, ring, cur - waiting + slots, slots, om, p, x,
-                                                             n);
+        SumrBasis b;
+        for (int j = 0; j <= waiting; ++j) b.q[j] = ring.slot(cur - waiting - 1 + j);
+        k_sumr_solution<<<dim3(1024, nf), 256, 0, c.stream>>>(rec, waiting, b, om, p, x, n);
         OVL_HIP(hipGetLastError());
         waiting = 0;
     };
-    double *part = (double *)c.buf("s_part", sizeof(double) * nblk * nf);
+    c.shrink = [&] {   // between two iterations: q and its predecessor stay
+        settle();
+        ring.keep(cur - 1, cur);
+        cur = 1;
+    };
     const double zeta = 1.0;
 
     std::vector<SumrField> F(nf);
@@ -605,18 +659,28 @@ static void sumr(Context &c, const ovl_zolo &z, const ovl_solver_params &prm, do
             if (st) st[f].sumr_iters += 1;
         }
         const dim3 grid(nblk, nf);
+        const bool tight = ring.size() == 2;   // the new q takes q_old's place: settle first
         SumrRec *now = rec + (size_t)waiting * nf;
+        if (tight) {
+            k_sumr_rec<<<1, 64, 0, c.stream>>>(k, now, nf);
+            OVL_HIP(hipGetLastError());
+            waiting = 1;
+            cur += 1;
+            settle();
+            cur -= 1;
+        }
+        double2 *next = ring.slot(cur + 1);
         if (lo && lp == OVL_F32)
-            k_sumr_basis<<<grid, 256, 0, c.stream>>>(k, now, slot(cur + 1), qt, (const float4 *)lo, c.g.V, part);
+            k_sumr_basis<<<grid, 256, 0, c.stream>>>(k, now, next, qt, (const float4 *)lo, c.g.V, part);
         else if (lo)
-            k_sumr_basis<<<grid, 256, 0, c.stream>>>(k, now, slot(cur + 1), qt, (const h8 *)lo, c.g.V, part);
+            k_sumr_basis<<<grid, 256, 0, c.stream>>>(k, now, next, qt, (const h8 *)lo, c.g.V, part);
         else
-            k_sumr_basis<<<grid, 256, 0, c.stream>>>(k, now, slot(cur + 1), qt, (const double2 *)u, c.g.V, part);
+            k_sumr_basis<<<grid, 256, 0, c.stream>>>(k, now, next, qt, (const double2 *)u, c.g.V, part);
         OVL_HIP(hipGetLastError());
-        cur = (cur + 1) % slots;
-        q = slot(cur);
-        qold = slot(cur - 1);
-        if (++waiting == group) settle();
+        cur = (cur + 1) % ring.size();
+        q = ring.slot(cur);
+        qold = ring.slot(cur - 1);
+        if (!tight && ++waiting >= ring.size() - 2) settle();
         // ||q|| monitoring (Sec. 2)
         const double *hq = sum_partials_host(c, part, nblk, nf);
         const std::vector<double> qn2(hq, hq + nf);
