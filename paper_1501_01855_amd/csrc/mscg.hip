@@ -946,7 +946,6 @@ static void sign_t(Context &c, double rho, const ovl_zolo &z, const void *in, vo
     int base = 0;
     for (int l = 1; l < nz; ++l)
         if (z.sigma[l] < z.sigma[base]) base = l;
-    k.base = base;
     k.s0 = z.sigma[base];
     for (int l = 0; l < nz; ++l) {
         k.sigma[l] = z.sigma[l];

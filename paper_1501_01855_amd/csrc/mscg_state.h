@@ -29,7 +29,7 @@ struct MscgCoef {
 };
 
 struct MscgConst {
-    int nz, base, maxiter, pad;
+    int nz, maxiter;
     double s0;
     double sigma[NZMAX], omega[NZMAX], tol2[NZMAX];
 };
