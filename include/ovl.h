@@ -250,7 +250,10 @@ ovl_status ovl_overlap_apply(ovl_context *ctx, double rho, double mu, const ovl_
  *     canonical [V][4][3][3] complex128 (same layout as the gauge field);
  *     overwritten.  Needs psi_dev.
  * At least one output must be given.  Each shifted inversion runs to
- * |zeta_l| ||r|| <= eta ||source||; prec OVL_F64 or OVL_F32 (FP32 storage
+ * |zeta_l| ||r|| <= eta ||source||; with both outputs D^dagger chi comes from
+ * the inversions on K gamma_5 chi, and these run further, to the accuracy at which
+ * their weighted sum errs by at most eta ||chi|| (eta times the smallest
+ * (sigma_l + a^2) / (omega_l n_z (|4 - rho| + 4)), if that is below 1).  prec OVL_F64 or OVL_F32 (FP32 storage
  * and arithmetic for the inversions, FP64 link accumulation).  The exactly
  * treated low modes are not differentiated: with low modes in the context this
  * returns OVL_ERR_UNSUPPORTED.  stats_host (may be null): one record. */
@@ -386,7 +389,7 @@ ovl_status ovl_stream_bench(ovl_context *ctx, int32_t kind, const void *src_dev,
                             int32_t reps, double *ms_host);
 
 /* Execution options of a context (value 0 = off, 1 = on, but for the last):
- *   OVL_OPT_GRAPHS   (default off) the multi-shift CG replays a graph of four
+ *   OVL_OPT_GRAPHS   (default off) the multi-shift CG replays a graph of eight
  *                    iterations per chunk after the first chunk (off: every
  *                    kernel is launched on its own); results are identical.
  *                    Off by default: on MI355X the replays were slower than
