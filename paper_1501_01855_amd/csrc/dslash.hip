@@ -1796,7 +1796,11 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     // Shorter ones take less time than the host takes to launch them, so that
     // events around the five would time the host (on 8^3 x 16 in FP16 such a
     // tuning took a 9.5 us variant for K^2 with a 5 us one on the list): they
-    // are timed one by one, by events attached to the dispatches.
+    // are timed one by one, by events attached to the dispatches; and so are
+    // launches that store for the caller, which run alone, after the packing: back
+    // to back they would cost the first call more (K on one FP32 field of 32^3 x 64
+    // 112 instead of 75 ms, H on twelve FP64 fields of 24^3 x 48 325 instead of
+    // 220) and choose no better.
     StencilArgs<ST> t = a;
     t.stop = nullptr;
     // with the store of the call: the canonical one, 192-byte rows of a site
@@ -1846,7 +1850,7 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     for (int v : ids) launch_by_id<ST, GT, EPI>(c, v, t, U, nf);   // warm-up
     for (int v : ids) ms_best[v] = single(v, 2);
     const float first = *std::min_element(ms_best.begin(), ms_best.end());
-    const bool small = first < REPS * 0.015f;
+    const bool small = first < REPS * 0.015f || a.canon;
     if (!small)
         for (int v : ids) ms_best[v] = ms_best[v] < 1.6f * first ? chain(v) : 1e30f;
     for (int round = 0; round < 2; ++round) {
