@@ -284,7 +284,8 @@ void overlap_f64(Context &c, double rho, double mu, const ovl_zolo &z, const dou
 // 2.75, where the statements together moved thirteen: 24^3 x 48, one field, 76 us
 // and a quarter of 281 us instead of 294 us; and with s left in FP16 the pass
 // before takes 47 instead of 66 us (a solve 1007 -> 963 ms).
-// Fields with act[f] = 0 are left untouched.
+// Fields with act[f] = 0 are left untouched; a slot filled without them holds no
+// q of theirs, and they need none until they start again.
 struct SumrCoef {
     double ar[MAXF], ai[MAXF], kr[MAXF], ki[MAXF], lr[MAXF], li[MAXF], er[MAXF], ei[MAXF], gr[MAXF], gi[MAXF],
         sigma[MAXF];
