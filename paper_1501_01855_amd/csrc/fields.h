@@ -344,9 +344,14 @@ __device__ __forceinline__ bool third_diff(double loaded, double rebuilt, int32_
     d = (int32_t)x;
     return d == x;
 }
+// (opaque to the compiler, as a loaded value is: seeing where it comes from, it
+// fuses other products of the hop, and the results differ in their last bits
+// from those on the full links)
 __device__ __forceinline__ double third_real(double rebuilt, int32_t d)
 {
-    return __longlong_as_double((long long)((uint64_t)__double_as_longlong(rebuilt) + (uint64_t)(int64_t)d));
+    double r = __longlong_as_double((long long)((uint64_t)__double_as_longlong(rebuilt) + (uint64_t)(int64_t)d));
+    asm("" : "+v"(r));
+    return r;
 }
 __device__ __forceinline__ void ld_link(const d2r12 *__restrict__ U, int64_t P, int mu, int64_t s, cplx<double> u[9])
 {

@@ -45,3 +45,31 @@ def test_links_bit_for_bit(dims, eps, off, two_row):
     link_bytes = ctx.profile_read(ovl.KERN_STENCIL, ovl.F64)["bytes"] / V - 384 * len(src)
     assert link_bytes == (480 if two_row else 576)
     ctx.close()
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 8), (5, 3, 7, 9)])
+def test_same_bits_on_either_form(dims):
+    """H and K on fields of noise, in every launch variant: the two-row form and
+    the full links give the same values to the last bit."""
+    ovl = require_gpu()
+    psi = to_dev(np.stack([synth.gaussian_source(dims, 50 + f) for f in range(3)]))
+    U = to_dev(synth.gauge_field(dims, 41, 0.3))
+    ran = 0
+    for v in range(ovl.N_STENCIL_VARIANTS):
+        out = []
+        for two_row in (1, 0):
+            ctx = ovl.Context(dims)
+            ctx.set_option(ovl.OPT_TWO_ROW_LINKS, two_row)
+            ctx.gauge_load(U)
+            try:
+                ctx.set_tuning({(ovl.F64 * 8 + e) * 64 + 3: v for e in (0, 1)})
+            except ovl.OvlError:
+                ctx.close()
+                break
+            out.append([to_host(ctx.wilson_dslash(psi)), to_host(ctx.kernel_K_apply(psi, 1.4))])
+            ctx.close()
+        if len(out) == 2:
+            ran += 1
+            for a, b in zip(*out):
+                assert np.array_equal(a, b), v
+    assert ran >= 9
