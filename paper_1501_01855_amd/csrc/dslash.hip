@@ -282,8 +282,8 @@ static constexpr double TWO_ROW_TOL = 0x1p-23;
 // operations per link, which the memory-bound stencil has to spare.  Rows
 // further off do not fit but on the smallest lattices; of links in SU(3) to
 // rounding about one in 3e8 does not.  D[mu] on 24^3 x 48: 72.8 -> 70.7 ms; H
-// on twelve fields 2.08 -> 2.05 ms; K on 3 fields of 15 x 9 x 21 x 27 75.6 ->
-// 73.6 us.
+// on twelve fields 2.08 -> 2.03 ms; K on 3 fields of 15 x 9 x 21 x 27 75.6 ->
+// 72.8 us.
 static constexpr double TWO_ROW_TOL64 = 0x1p-43;
 
 void pack_gauge(Context &c, const double *canon)
@@ -1777,10 +1777,12 @@ static void launch_by_id(Context &c, int id, const StencilArgs<ST> &a, const GT 
     }
 }
 
-// The scratch output of timed launches.
-static void reserve_tuning(Context &c, int prec, int nf)
+// The scratch of timed launches: their output and, where they store for the
+// caller, their input.
+static void reserve_tuning(Context &c, int prec, bool canon, int nf)
 {
-    c.buf("tune_out", field_bytes(c.g, prec) * nf);
+    c.buf("tune_out", field_bytes(c.g, canon ? OVL_F64 : prec) * nf);
+    if (canon) c.buf("tune_in", field_bytes(c.g, prec) * nf);
     c.buf("tune_part", sizeof(double) * 3 * (size_t)nf * stencil_tiles_max(c.g));
 }
 
@@ -1800,10 +1802,9 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     // events around the five would time the host (on 8^3 x 16 in FP16 such a
     // tuning took a 9.5 us variant for K^2 with a 5 us one on the list): they
     // are timed one by one, by events attached to the dispatches; and so are
-    // launches that store for the caller, which run alone, after the packing: back
-    // to back they would cost the first call more (K on one FP32 field of 32^3 x 64
-    // 112 instead of 75 ms, H on twelve FP64 fields of 24^3 x 48 325 instead of
-    // 220) and choose no better.
+    // launches that store for the caller, each after a pass that writes its input,
+    // as the packing does in use (K on 3 fields of 15 x 9 x 21 x 27: 59 us with the
+    // variant that is best without, 57 with the one that is best so).
     StencilArgs<ST> t = a;
     t.stop = nullptr;
     // with the store of the call: the canonical one, 192-byte rows of a site
@@ -1811,9 +1812,10 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     // another variant hides it best (H and K on twelve FP16 fields of 24^3 x 48:
     // 963 us with the variant chosen under the packed store, 763 with the one
     // chosen under its own; FP32, one field: 118 and 96 us)
-    reserve_tuning(c, a.canon ? OVL_F64 : prec, nf);   // held since before the links were chosen
+    reserve_tuning(c, prec, a.canon != nullptr, nf);   // held since before the links were chosen
     t.canon = a.canon ? (double2 *)c.pool["tune_out"].p : nullptr;
     t.out = (ST *)c.pool["tune_out"].p;
+    if (a.canon) t.in = (const ST *)c.pool["tune_in"].p;
     t.partial = (double *)c.pool["tune_part"].p;
     constexpr int REPS = 5;
     struct Events {
@@ -1826,6 +1828,7 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
         for (int r = 0; r < reps; ++r) {
             pe.a = ev.e[2 * r];
             pe.b = ev.e[2 * r + 1];
+            if (a.canon) copy_fields(c, a.in, c.pool["tune_in"].p, nf, prec);   // as the packing leaves it
             launch_by_id<ST, GT, EPI>(c, v, t, U, nf, &pe);
         }
         OVL_HIP(hipEventSynchronize(pe.b));
@@ -1850,6 +1853,7 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     for (int v = 0; v < N_VARIANTS; ++v)
         if (stencil_variant_ok(c.g, prec, v)) ids.push_back(v);
     std::vector<float> ms_best(N_VARIANTS, 1e30f);
+    if (a.canon) copy_fields(c, a.in, c.pool["tune_in"].p, nf, prec);
     for (int v : ids) launch_by_id<ST, GT, EPI>(c, v, t, U, nf);   // warm-up
     for (int v : ids) ms_best[v] = single(v, 2);
     const float first = *std::min_element(ms_best.begin(), ms_best.end());
@@ -1865,7 +1869,7 @@ static int tuned_variant(Context &c, const StencilArgs<ST> &a, const GT *U, int 
     for (int v : ids)
         if (ms_best[v] < ms_best[best]) best = v;
     OVL_HIP(hipGetLastError());
-    c.idle({"tune_out", "tune_part"});
+    c.idle({"tune_out", "tune_in", "tune_part"});
     return c.tuned[key] = best;
 }
 
@@ -1908,7 +1912,7 @@ void stencil(Context &c, int epi, int prec, const void *in, void *out, int nf, d
     // room for timing this launch before the links are chosen: an allocation may
     // cost the FP64 two-row links
     if (c.autotune && !c.no_alloc && !c.tuned.count(tuning_key(prec, epi == EPI_K && canon ? TUNE_K_CANON : epi, nf)))
-        reserve_tuning(c, canon ? OVL_F64 : prec, nf);
+        reserve_tuning(c, prec, canon != nullptr, nf);
     if (prec == OVL_F64) {
         StencilArgs<double2> a{c.g, (const double2 *)in, (double2 *)out, (const double2 *)aux,
                                (const double2 *)aux2, 4.0 - rho, sigma, partial, stop, it, itb, canon};
