@@ -47,14 +47,18 @@ bool Context::reclaim(int level)
 hipError_t Context::device_alloc(void **p, size_t bytes)
 {
     hipError_t e = hipErrorOutOfMemory;
+    bool limited = false;
     for (int level = -1; level < 3; ++level) {
         if (level >= 0 && !reclaim(level)) continue;
-        if (ws_limit && (size_t)bytes_held + bytes > ws_limit) continue;
+        limited = ws_limit && (size_t)bytes_held + bytes > ws_limit;
+        if (limited) continue;
         e = hipMalloc(p, bytes);
         if (e == hipSuccess) return e;
         (void)hipGetLastError();   // reported by the caller, not by the next launch
     }
     *p = nullptr;
+    OVL_REQUIRE(!limited, OVL_ERR_NOMEM,
+                "the workspace limit leaves no room for " + std::to_string(bytes) + " bytes more");
     return e;
 }
 

@@ -167,3 +167,31 @@ def test_solve(ladder, restarts):
     ctx.close()
     fields = 3 * (2 + 4 + 7 + 1 + 2 * max(steps) + 5 + z.nz + (0 if ladder == "f64" else 2 * 0.5 + 1))
     _descend(ovl, lambda ctx, zg: ctx.solve(dev, zg, p), check, fields * FIELD, 3 * FIELD)
+
+
+def test_links_and_low_modes_beyond_the_limit():
+    """A load of links that the limit does not allow, then one that it does; the
+    low modes likewise."""
+    ovl = require_gpu()
+    U, z, sign = _problem()
+    links = _links(ovl)
+    ctx = ovl.Context(DIMS)
+    ctx.set_option(ovl.OPT_AUTOTUNE, 0)
+    ctx.set_option(ovl.OPT_WORKSPACE_KIB, links // 2048)
+    for _ in range(2):
+        with pytest.raises(ovl.OvlError) as e:
+            ctx.gauge_load(to_dev(U))
+        assert e.value.code == -3
+    ctx.set_option(ovl.OPT_WORKSPACE_KIB, int(links + (7 + z.nz) * FIELD + SMALL) // 1024)
+    ctx.gauge_load(to_dev(U))
+    psi = synth.gaussian_source(DIMS, 64)
+    zg = ovl.zolo_from(z.nz, z.a, z.b, z.delta, z.omega, z.sigma)
+    got = to_host(ctx.sign(to_dev(psi), RHO, zg, 1e-11)[0])
+    assert norm(got - sign(psi, 1e-13)) <= 2e-11 * norm(psi)
+    import torch
+    many = torch.zeros((40, V, 4, 3), dtype=torch.complex128, device="cuda")
+    with pytest.raises(ovl.OvlError) as e:
+        ctx.lowmodes_set([1.0] * 40, many)
+    assert e.value.code == -3
+    assert np.array_equal(to_host(ctx.sign(to_dev(psi), RHO, zg, 1e-11)[0]), got)
+    ctx.close()
